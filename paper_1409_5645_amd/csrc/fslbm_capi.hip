@@ -39,6 +39,10 @@ struct fslbm_ctx {
   int rcap = 0;
   bool reorder = false;
   bool list_ok = false;
+  // barrier words of the kernels whose workgroups meet: a launch counts in one
+  // and zeroes the other for the next
+  unsigned long long* bars = nullptr;
+  int bar_flip = 0;
   double* reservoir;
   double* kappa = nullptr;  // surface tension only
   double* khf = nullptr;    // surface tension with plic = 2 only
@@ -85,8 +89,10 @@ thread_local std::string g_init_error;
 constexpr size_t ALIGN = 256;
 size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
+size_t storage_bytes(int precision) { return precision == FSLBM_FP64 ? 8 : (precision == FSLBM_FP32 ? 4 : 2); }
+
 struct Layout {
-  size_t aux, epochs[4], lists[7], counters, scalars, extent, wall_t, kappa, khf, islot, rbuf, rcap, total;
+  size_t aux, epochs[4], lists[7], counters, scalars, extent, wall_t, kappa, khf, islot, rbuf, rcap, bars, total;
 };
 
 // Entries of the list-ordered population buffer of the interface-first step:
@@ -145,6 +151,8 @@ Layout layout(size_t N, bool kappa, bool hf, size_t s, bool reorder) {
   if (reorder) o = align_up(o + 4 * N);
   L.rbuf = o;
   if (reorder) o = align_up(o + (size_t)Q * s * L.rcap);
+  L.bars = o;
+  o = align_up(o + 2 * ALIGN);
   L.total = o;
   return L;
 }
@@ -175,8 +183,6 @@ fslbm_status check_params(const fslbm_params* p, std::string& why) {
     if (!std::isfinite(p->g[a])) { why = "g must be finite"; return FSLBM_E_INVALID; }
   return FSLBM_OK;
 }
-
-size_t storage_bytes(int precision) { return precision == FSLBM_FP64 ? 8 : (precision == FSLBM_FP32 ? 4 : 2); }
 
 fslbm_status dev_fail(fslbm_ctx* c, hipError_t e, const char* what) {
   std::string m = std::string(what) + ": " + hipGetErrorString(e);
@@ -323,6 +329,7 @@ fslbm_status init_impl(const fslbm_params* p, const fslbm_buffers* b, void* work
     if (const char* e = std::getenv("FSLBM_REORDER")) c->reorder = std::atoi(e) != 0 && p->precision != FSLBM_FP16S;
     if (const char* e = std::getenv("FSLBM_RCAP")) c->rcap = std::max(0, std::min(c->rcap, std::atoi(e)));
   }
+  c->bars = (unsigned long long*)(w + L.bars);
   {
     double tab[6 * Q];
     wall_table(*p, tab);
@@ -346,6 +353,8 @@ fslbm_status init_impl(const fslbm_params* p, const fslbm_buffers* b, void* work
   if ((e = launch_fill_i32(c->err, 16, 0, st)) != hipSuccess) return fail(dev_fail(c, e, "init scalars"));
   if ((e = launch_extent_init(c->ext_dev, st)) != hipSuccess) return fail(dev_fail(c, e, "init extent"));
   if ((e = launch_fill_f64(c->reservoir, 2, 0.0, st)) != hipSuccess) return fail(dev_fail(c, e, "init scalars"));
+  if ((e = launch_fill_i32((int32_t*)c->bars, 2 * ALIGN / sizeof(int32_t), 0, st)) != hipSuccess)
+    return fail(dev_fail(c, e, "init barriers"));
   if ((e = launch_check_flags(c->flags, c->com.grid, c->err, st)) != hipSuccess) return fail(dev_fail(c, e, "check flags"));
   int32_t herr = 0;
   if ((e = hipMemcpyAsync(&herr, c->err, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream)) != hipSuccess)
@@ -517,6 +526,14 @@ fslbm_status health(fslbm_ctx* c, double sc[2], int32_t cn[8], int32_t last[NCOU
   return FSLBM_OK;
 }
 
+// The health check after a step whose count is a multiple of check_every.
+fslbm_status check_due(fslbm_ctx* c) {
+  if (c->check_every <= 0 || c->step % c->check_every != 0) return FSLBM_OK;
+  double sc[2];
+  int32_t cn[8], last[NCOUNT];
+  return health(c, sc, cn, last);
+}
+
 // Rows the sweep of the next step launches (SweepArgs box), from the latest
 // fluid extent that has arrived, widened by one cell per step since it was
 // measured; a new measurement (of the rows of this box) starts every
@@ -579,6 +596,79 @@ hipError_t sweep_box(fslbm_ctx* c, SweepArgs& s) {
   return hipSuccess;
 }
 
+// Arguments of the next step (the sweep's row box, and whether the interface
+// kernel goes first, are left to the caller).
+void step_args(const fslbm_ctx* c, StepLaunch& L) {
+  const int a = c->cur, b = 1 - c->cur;
+  SweepArgs& s = L.sweep;
+  s.c = c->com;
+  s.fin = c->f[a];
+  s.fout = c->f[b];
+  s.flags = c->flags;
+  s.mass_in = c->mass;
+  s.mass = c->mass;
+  s.phi_in = c->phi[a];
+  s.phi_out = c->phi[b];
+  s.aux = c->aux;
+  s.f_epoch = c->f_epoch;
+  s.listF = c->listF;
+  s.listE = c->listE;
+  s.listI = c->listI;
+  s.counters = c->counters + (c->step & 1) * NCOUNT;
+  s.counters_next = c->counters + ((c->step + 1) & 1) * NCOUNT;
+  s.thr_hi = c->thr_hi;
+  s.thr_lo = c->thr_lo;
+  s.step = c->step;
+  s.freeze = (c->p.freeze || c->p.hold_fill) ? 1 : 0;  // a held surface keeps its classes
+  s.hold = c->p.hold_fill ? 1 : 0;
+  s.cpr = 0;
+  s.pairs = c->pairs;
+  s.quad = c->quad;
+  s.u_out = nullptr;
+  s.kappa = c->kappa;
+  s.khf = c->khf;
+  s.wall_t = c->wall_t;
+  s.wcells = c->wcells;
+  s.wdelta = c->wdelta;
+  s.wuw = c->wuw;
+  s.nwall = c->nwall > 0 ? c->nwall : 0;
+  s.surf_n = c->surf_n;
+  s.surf_d = c->surf_d;
+  ConvArgs& v = L.conv;
+  v.c = c->com;
+  v.fout = c->f[b];
+  v.flags = c->flags;
+  v.mass = c->mass;
+  v.phi_out = c->phi[b];
+  v.aux = c->aux;
+  v.f_epoch = c->f_epoch;
+  v.new_epoch = c->new_epoch;
+  v.recv_epoch = c->recv_epoch;
+  v.conv_epoch = c->conv_epoch;
+  v.listF = c->listF;
+  v.listE = c->listE;
+  v.listEP = c->listEP;
+  v.listNI = c->listNI;
+  v.listNL = c->listNL;
+  v.listR = c->listR;
+  v.counters = s.counters;
+  v.reservoir = c->reservoir;
+  v.step = c->step;
+  v.listI = c->listI;
+  v.islot = c->islot;
+  v.counters_next = s.counters_next;
+  v.bar = c->bars + c->bar_flip * (ALIGN / sizeof(unsigned long long));
+  v.bar_next = c->bars + (1 - c->bar_flip) * (ALIGN / sizeof(unsigned long long));
+  s.islot = c->islot;
+  s.rbuf = c->rbuf;
+  s.rcap = c->rcap;
+  L.stream = (void*)c->stream;
+}
+
+// Whether moving walls, surface tension, PLIC, solid walls or a prescribed
+// surface take the step off the plain kernels.
+bool extra_step(const Common& m) { return m.moving || m.sigma != 0.0 || m.plic || m.solid || m.surface; }
+
 }  // namespace
 
 extern "C" {
@@ -597,75 +687,13 @@ fslbm_status fslbm_step(fslbm_ctx* c, int32_t n, int32_t rule) {
   }
   for (int32_t i = 0; i < n; ++i) {
     StepLaunch L{};
-    const int a = c->cur, b = 1 - c->cur;
+    step_args(c, L);
     SweepArgs& s = L.sweep;
-    s.c = c->com;
-    s.fin = c->f[a];
-    s.fout = c->f[b];
-    s.flags = c->flags;
-    s.mass_in = c->mass;
-    s.mass = c->mass;
-    s.phi_in = c->phi[a];
-    s.phi_out = c->phi[b];
-    s.aux = c->aux;
-    s.f_epoch = c->f_epoch;
-    s.listF = c->listF;
-    s.listE = c->listE;
-    s.listI = c->listI;
-    s.counters = c->counters + (c->step & 1) * NCOUNT;
-    s.counters_next = c->counters + ((c->step + 1) & 1) * NCOUNT;
-    s.thr_hi = c->thr_hi;
-    s.thr_lo = c->thr_lo;
-    s.step = c->step;
-    s.freeze = (c->p.freeze || c->p.hold_fill) ? 1 : 0;  // a held surface keeps its classes
-    s.hold = c->p.hold_fill ? 1 : 0;
-    s.cpr = 0;
-    s.pairs = c->pairs;
-    s.quad = c->quad;
-    s.u_out = nullptr;
-    s.kappa = c->kappa;
-    s.khf = c->khf;
-    s.wall_t = c->wall_t;
-    s.wcells = c->wcells;
-    s.wdelta = c->wdelta;
-    s.wuw = c->wuw;
-    s.nwall = c->nwall > 0 ? c->nwall : 0;
-    s.surf_n = c->surf_n;
-    s.surf_d = c->surf_d;
     // the plain step with the four-lane interface kernel runs it before the
     // sweep (the other variants after it)
-    const bool extra = s.c.moving || s.c.sigma != 0.0 || s.c.plic || s.c.solid || s.c.surface;
-    const bool order = c->reorder && c->quad && !extra;
-    s.order = order ? 1 : 0;
-    s.islot = c->islot;
-    s.rbuf = c->rbuf;
-    s.rcap = c->rcap;
+    const bool order = c->reorder && c->quad && !extra_step(s.c);
+    s.order = L.conv.order = order ? 1 : 0;
     HIPCHK(c, sweep_box(c, s), "extent");
-    ConvArgs& v = L.conv;
-    v.c = c->com;
-    v.fout = c->f[b];
-    v.flags = c->flags;
-    v.mass = c->mass;
-    v.phi_out = c->phi[b];
-    v.aux = c->aux;
-    v.f_epoch = c->f_epoch;
-    v.new_epoch = c->new_epoch;
-    v.recv_epoch = c->recv_epoch;
-    v.conv_epoch = c->conv_epoch;
-    v.listF = c->listF;
-    v.listE = c->listE;
-    v.listEP = c->listEP;
-    v.listNI = c->listNI;
-    v.listNL = c->listNL;
-    v.listR = c->listR;
-    v.counters = s.counters;
-    v.reservoir = c->reservoir;
-    v.step = c->step;
-    v.order = s.order;
-    v.listI = c->listI;
-    v.islot = c->islot;
-    v.counters_next = s.counters_next;
-    L.stream = (void*)c->stream;
     if (order) {
       // the interface list of the current classes, when no step has left it
       if (!c->list_ok)
@@ -691,16 +719,15 @@ fslbm_status fslbm_step(fslbm_ctx* c, int32_t n, int32_t rule) {
       if (c->kappa) HIPCHK(c, launch_curvature(L), "curvature launch");
       HIPCHK(c, launch_iface(L, c->p.precision, rule), "interface launch");
     }
-    if (!s.freeze) HIPCHK(c, launch_convert(L, c->p.precision), "conversion launch");
-    c->list_ok = order;
-    c->cur = b;
-    c->step += 1;
-    if (c->check_every > 0 && c->step % c->check_every == 0) {
-      double sc[2];
-      int32_t cn[8], last[NCOUNT];
-      const fslbm_status hs = health(c, sc, cn, last);
-      if (hs != FSLBM_OK) return hs;
+    if (!s.freeze) {
+      HIPCHK(c, launch_convert(L, c->p.precision), "conversion launch");
+      c->bar_flip = 1 - c->bar_flip;
     }
+    c->list_ok = order;
+    c->cur = 1 - c->cur;
+    c->step += 1;
+    const fslbm_status hs = check_due(c);
+    if (hs != FSLBM_OK) return hs;
   }
   return FSLBM_OK;
 }

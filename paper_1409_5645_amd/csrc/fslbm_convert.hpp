@@ -1,0 +1,277 @@
+// The conversions of a step after its interface cells are done (lists F and E
+// built): three passes, each over the lists the passes before it made, with a
+// barrier between them.
+//
+//   mark    E' = E minus N(F); claims the new interface cells: gas cells next
+//           to filled cells, liquid cells next to E' cells.
+//   share   excess of the filled and E' cells split over the neighbours that
+//           are interface cells after the conversions (receivers listed); the
+//           new interface cells initialised.
+//   gather  receivers add their shares in ascending link order, fill refresh;
+//           new cell classes.
+//
+// Thirty-two lanes take one listed cell, lane q its link q: a cell's eighteen
+// neighbours are loaded by eighteen lanes at once, and what is needed of all
+// of them is a ballot.  Few cells convert in a step, so the passes are chains
+// of memory round trips through code that is not in the instruction cache:
+// each pass is one or two trips and a few hundred instructions.  (With one
+// thread per cell and link, every thread walking the eighteen neighbours in
+// unrolled code, the passes took 8, 5 and 4 us for five converted cells.)
+//
+// A few converted cells are left to one workgroup (SOLO: list lengths in LDS,
+// atomics that need not leave its L2), many are spread over the grid.
+#pragma once
+
+#include "fslbm_barrier.hpp"
+#include "fslbm_device.hpp"
+#include "fslbm_internal.hpp"
+#include "fslbm_quad.hpp"
+#include "fslbm_stencil.hpp"
+
+namespace fslbm {
+
+constexpr int CLANES = 32;  // lanes per listed cell
+
+template <bool SOLO>
+__device__ __forceinline__ int exchange(int32_t* p, int v) {
+  return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, SOLO ? __HIP_MEMORY_SCOPE_WORKGROUP : __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The lane of a link: q = lane, its direction (0 for the rest lane and the
+// idle lanes 19 .. 31) and that of the odd link of its pair.
+struct LinkLane {
+  int q, c[3], d[3];
+  bool link;
+  __device__ __forceinline__ LinkLane() {
+    q = (int)threadIdx.x & (CLANES - 1);
+    link = q >= 1 && q < Q;
+    pair_dir(link ? (q - 1) >> 1 : 0, d);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      d[k] = link ? d[k] : 0;
+      c[k] = (q & 1) ? d[k] : -d[k];
+    }
+  }
+  // the lane's neighbour of cell idx (-1 beyond a wall, and for lanes without a link)
+  __device__ __forceinline__ int neighbour(const Grid& g, int idx) const {
+    int x, y, z;
+    coords(g, idx, x, y, z);
+    return link ? neighbor(g, x, y, z, c[0], c[1], c[2]) : -1;
+  }
+};
+
+// ballot over the lanes of the cell
+__device__ __forceinline__ uint32_t cell_ballot(bool p) {
+  return (uint32_t)(__ballot(p) >> (threadIdx.x & (unsigned)CLANES));
+}
+
+// value of lane i of the cell's lanes
+template <class T>
+__device__ __forceinline__ T cell_lane(T v, int i) {
+  return __shfl(v, i, CLANES);
+}
+
+// Mark of an E' cell in new_epoch: below every step stamp (>= 0) and the
+// initial -1, and distinct for every step.  E' cells are interface cells and
+// new_epoch's step stamps go to gas and liquid cells only.
+__device__ __forceinline__ int ep_stamp(int step) { return -2 - step; }
+
+template <bool SOLO>
+__device__ __forceinline__ void mark_pass(const ConvArgs& a, int step, int32_t* cnt, int nF, int nE, unsigned tid,
+                                          unsigned nth) {
+  const Grid& g = a.c.grid;
+  const LinkLane ln;
+  for (unsigned e = tid / CLANES; e < (unsigned)(nF + nE); e += nth / CLANES) {
+    const bool filled = e < (unsigned)nF;
+    const int c = filled ? a.listF[e] : a.listE[e - (unsigned)nF];
+    const int s = ln.neighbour(g, c);
+    const uint8_t ts = s >= 0 ? a.flags[s] : (uint8_t)SOLID;
+    const int fe = s >= 0 ? a.f_epoch[s] : -1;
+    // E' = E minus N(F)
+    const bool drop = !filled && cell_ballot(fe == step) != 0u;
+    const bool ep = !filled && !drop;
+    if (ep && ln.q == 0) a.new_epoch[c] = ep_stamp(step);
+    wave_append(ep && ln.q == 0, &cnt[C_EP], a.listEP, c);
+    // Which lane wins a new cell's mark does not change the result
+    bool win = false;
+    if (filled ? ts == GAS : (ep && ts == LIQ)) win = exchange<SOLO>(&a.new_epoch[s], step) != step;
+    wave_append(win && filled, &cnt[C_NI], a.listNI, s);
+    wave_append(win && !filled, &cnt[C_NL], a.listNL, s);
+  }
+}
+
+// Whether cell t is an interface cell after this step's conversions: a new
+// interface cell, or an interface cell of time t that neither filled nor is in
+// E'.
+__device__ __forceinline__ bool iface_after(const ConvArgs& a, int step, int t) {
+  const int ne = a.new_epoch[t];
+  const int fe = a.f_epoch[t];
+  const uint8_t fl = a.flags[t];
+  return (ne == step) | ((fl == IFACE) & (fe != step) & (ne != ep_stamp(step)));
+}
+
+// Excess of a converted cell c: split over its eligible neighbours (or handed
+// to the reservoir), which are listed as receivers.
+template <bool SOLO>
+__device__ __forceinline__ void share_cell(const ConvArgs& a, int step, int32_t* cnt, const LinkLane& ln, int c,
+                                           bool filled) {
+  const int s = ln.neighbour(a.c.grid, c);
+  const bool el = (s >= 0) & iface_after(a, step, s >= 0 ? s : c);
+  const double m = a.mass[c], r = a.aux[4 * (size_t)c];
+  const int n_elig = __popc(cell_ballot(el));
+  if (ln.q == 0) {
+    const double ex = filled ? m - r : m;
+    if (n_elig == 0) {
+      atomicAdd(a.reservoir, ex);
+      if (filled) a.mass[c] = ex;
+    } else {
+      a.mass[c] = ex / (double)n_elig;
+      a.conv_epoch[c] = step;
+    }
+  }
+  bool first = false;
+  if (el) first = exchange<SOLO>(&a.recv_epoch[s], step) != step;
+  wave_append(first, &cnt[C_R], a.listR, s);
+}
+
+// New interface cell from gas: f = f^eq of the mean collision density and
+// velocity of the non-gas neighbours (summed in link order), mass 0.
+template <class F>
+__device__ __forceinline__ void init_from_gas(const ConvArgs& a, const LinkLane& ln, int c) {
+  using R = typename F::R;
+  using S = typename F::S;
+  constexpr bool SH = F::shifted;
+  const int s = ln.neighbour(a.c.grid, c);
+  const uint8_t ts = s >= 0 ? a.flags[s] : (uint8_t)GAS;
+  const double4 v = *reinterpret_cast<const double4*>(a.aux + 4 * (size_t)(s >= 0 ? s : c));
+  uint32_t m = cell_ballot(ts != GAS && ts != SOLID);
+  double rs = 0.0, us[3] = {0.0, 0.0, 0.0};
+  const int cnt = __popc(m);
+  for (; m != 0u; m &= m - 1u) {
+    const int i = __ffs((int)m) - 1;
+    rs = rs + cell_lane(v.x, i);
+    us[0] = us[0] + cell_lane(v.y, i);
+    us[1] = us[1] + cell_lane(v.z, i);
+    us[2] = us[2] + cell_lane(v.w, i);
+  }
+  const double rbar = rs / (double)cnt;
+  const Consts<R>& k = pick_consts<R>(a.c);
+  const bool incomp = a.c.incomp, stokes = a.c.stokes;
+  const R rho_s = SH ? (R)(rbar - 1.0) : (R)rbar;
+  const R rho0 = rho0_of<R, SH>(rho_s, incomp);
+  R u[3], w[3], d[3];  // equilibrium_post, a link per lane
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    u[i] = (R)(us[i] / (double)cnt);
+    w[i] = u[i] + k.hg[i];
+    d[i] = R(ln.d[i]);
+  }
+  const R wq = R(ln.q == 0 ? WD[0] : (ln.q <= 6 ? WD[1] : WD[7]));
+  const R ep = e_plus_w(wq, ddot(d, u), rho_s, rho0, incomp, stokes, usq_of(u));
+  R cu = ddot(d, w);
+  if (!incomp) cu = rho0 * cu;
+  const R em = R(ln.q <= 6 ? W3D[1] : W3D[7]) * cu;
+  const R out = ln.q == 0 ? ep : ((ln.q & 1) ? ep + em : ep - em);
+  if (ln.q < Q) F::store(reinterpret_cast<S*>(a.fout) + ((size_t)ln.q * a.c.grid.N + c), out, a.c.scale);
+  if (ln.q == 0) {
+    a.mass[c] = 0.0;
+    a.aux[4 * (size_t)c] = rbar;
+  }
+}
+
+// A new interface cell from liquid keeps its populations (of time t+1); m = rho.
+template <class F>
+__device__ __forceinline__ void init_from_liquid(const ConvArgs& a, const LinkLane& ln, int c) {
+  using R = typename F::R;
+  using S = typename F::S;
+  const int q = ln.q < Q ? ln.q : 0;
+  const R f = F::load(reinterpret_cast<const S*>(a.fout) + ((size_t)q * a.c.grid.N + c), a.c.inv_scale);
+  double r = F::shifted ? 0.0 : (double)cell_lane(f, 0);
+  for (int i = F::shifted ? 0 : 1; i < Q; ++i) r = r + (double)cell_lane(f, i);
+  if (F::shifted) r = 1.0 + r;
+  if (ln.q == 0) {
+    a.mass[c] = r;
+    a.aux[4 * (size_t)c] = r;
+  }
+}
+
+template <class F, bool SOLO>
+__device__ __forceinline__ void share_pass(const ConvArgs& a, int step, int32_t* cnt, int nF, int nEP, int nNI,
+                                           int nNL, unsigned tid, unsigned nth) {
+  const LinkLane ln;
+  const int n0 = nF + nEP, n1 = n0 + nNI, n2 = n1 + nNL;
+  for (int e = (int)(tid / CLANES); e < n2; e += (int)(nth / CLANES)) {
+    if (e < n0) share_cell<SOLO>(a, step, cnt, ln, e < nF ? a.listF[e] : a.listEP[e - nF], e < nF);
+    else if (e < n1) init_from_gas<F>(a, ln, a.listNI[e - n0]);
+    else init_from_liquid<F>(a, ln, a.listNL[e - n1]);
+  }
+}
+
+// Receivers, and the new cell classes (with the interface kernel first, the
+// new interface cells also join the next list).
+__device__ __forceinline__ void gather_pass(const ConvArgs& a, int step, int nR, int nF, int nEP, int nNI, int nNL,
+                                            unsigned tid, unsigned nth) {
+  const LinkLane ln;
+  for (int e = (int)(tid / CLANES); e < nR; e += (int)(nth / CLANES)) {
+    const int r = a.listR[e];
+    const int s = ln.neighbour(a.c.grid, r);
+    const int ep = s >= 0 ? a.conv_epoch[s] : -1;
+    const double mn = a.mass[s >= 0 ? s : r];
+    const double rho = a.aux[4 * (size_t)r];
+    double m = cell_lane(mn, 0);  // the rest lane has the receiver's own
+    for (uint32_t b = cell_ballot(ep == step); b != 0u; b &= b - 1u) m = m + cell_lane(mn, __ffs((int)b) - 1);
+    if (ln.q == 0) {
+      a.mass[r] = m;
+      a.phi_out[r] = m / rho;
+    }
+  }
+  const int n1 = nF + nEP, n2 = n1 + nNI, n3 = n2 + nNL;
+  for (int j = (int)tid; j < n3; j += (int)nth) {
+    const int cell = j < nF ? a.listF[j] : (j < n1 ? a.listEP[j - nF] : (j < n2 ? a.listNI[j - n1] : a.listNL[j - n2]));
+    const bool join = j >= n1;
+    a.flags[cell] = j < nF ? LIQ : (j < n1 ? GAS : IFACE);
+    if (a.order) {
+      const int pos = wave_append_at(join, &a.counters_next[C_I], a.listI, cell);
+      if (join) a.islot[cell] = pos;
+    }
+  }
+}
+
+// All the conversions of a step by the threads of a grid, after its lists F and
+// E are complete and visible (nF, nE their lengths, the same in every thread).
+// Up to SOLO_CELLS converted cells the first workgroup does them alone, the
+// others pass: its barriers are cheap, those of the grid (and its atomics,
+// which leave the L2) are not.
+template <class F, int BLOCK>
+__device__ __forceinline__ void convert_all(const ConvArgs& v, int step, int nF, int nE, GridBarrier& grid) {
+  __shared__ int32_t sc[NCOUNT];
+  const unsigned lid = threadIdx.x;
+  if (nF + nE <= SOLO_CELLS) {
+    if (blockIdx.x != 0) return;
+    if (lid < NCOUNT) sc[lid] = 0;
+    __syncthreads();
+    mark_pass<true>(v, step, sc, nF, nE, lid, BLOCK);
+    block_meet();
+    const int nEP = sc[C_EP], nNI = sc[C_NI], nNL = sc[C_NL];
+    share_pass<F, true>(v, step, sc, nF, nEP, nNI, nNL, lid, BLOCK);
+    block_meet();
+    const int nR = sc[C_R];
+    gather_pass(v, step, nR, nF, nEP, nNI, nNL, lid, BLOCK);
+    if (lid == 0) {
+      v.counters[C_EP] = nEP;
+      v.counters[C_NI] = nNI;
+      v.counters[C_NL] = nNL;
+      v.counters[C_R] = nR;
+    }
+    return;
+  }
+  const unsigned tid = blockIdx.x * BLOCK + lid, nth = gridDim.x * BLOCK;
+  mark_pass<false>(v, step, v.counters, nF, nE, tid, nth);
+  grid.meet(false);
+  const int nEP = peek(&v.counters[C_EP]), nNI = peek(&v.counters[C_NI]), nNL = peek(&v.counters[C_NL]);
+  share_pass<F, false>(v, step, v.counters, nF, nEP, nNI, nNL, tid, nth);
+  grid.meet(false);
+  gather_pass(v, step, peek(&v.counters[C_R]), nF, nEP, nNI, nNL, tid, nth);
+}
+
+}  // namespace fslbm

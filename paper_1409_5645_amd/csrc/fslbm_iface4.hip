@@ -64,16 +64,6 @@ __device__ __forceinline__ R bq(const R (&A)[3], const R (&B)[3], R r0) {
   }
 }
 
-// even equilibrium e+ of a link with c.u = cu and weight wq (Eq. eqEven), the
-// operations of e_plus<q>
-template <class R>
-__device__ __forceinline__ R e_plus_w(R wq, R cu, R rho_s, R rho0, bool incomp, bool stokes, R usq) {
-  if (stokes) return wq * rho_s;
-  R nl = R(4.5) * (cu * cu) - R(1.5) * usq;
-  if (!incomp) nl = rho0 * nl;
-  return wq * (rho_s + nl);
-}
-
 // c c : S for a direction d (components in {-1, 0, 1}), the operations of c_S_c<q>
 template <class R>
 __device__ __forceinline__ R dSd(const int (&d)[3], const R (&S)[6]) {

@@ -10,19 +10,16 @@
 //   The plain step of the FP32 form runs k_iface4 first, on the list the
 //   step before built, and k_sweep stores its populations (the
 //   interface-first order of SweepArgs::order).
-//   k_mark    E' = E minus N(F); new interface cells from gas next to filled
-//             cells (initialised from their interface neighbours) and from
-//             liquid next to E' cells.
-//   k_share   excess of the filled and E' cells split over the neighbours
-//             that are interface cells after the conversions; receiver list.
-//   k_gather  receivers add the shares in ascending link order; fill refresh;
-//             new cell classes.
+//   k_convert the conversions, in three passes with barriers between them
+//             (fslbm_convert.hpp): E' and the new interface cells; excess
+//             shares, receivers, initialisation; receivers' sums, new classes.
 // Membership marks are step-stamped int arrays ("epochs"), so nothing needs to
 // be cleared between steps; list counters are double buffered by step parity
 // and the sweep of step t (the interface kernel, when it runs first) zeroes
 // the set of step t+1.  The cell classes keep
-// their values of time t until k_gather: k_share takes the classes after the
-// conversions from the marks (iface_after).
+// their values of time t until the last pass: the share pass takes the classes
+// after the conversions from the marks (iface_after).
+#include "fslbm_convert.hpp"
 #include "fslbm_device.hpp"
 #include "fslbm_internal.hpp"
 #include "fslbm_stencil.hpp"
@@ -470,246 +467,21 @@ __global__ __launch_bounds__(IBLOCK) void k_curvature_hf(SweepArgs a) {
 }
 
 // ------------------------------------------------------------ conversions
-// Classes and auxiliary rows of the 18 neighbours of a new interface cell c
-// from gas (a neighbour beyond a wall reads the cell's own row and counts as
-// gas).  Split from the arithmetic so that the loads can go out before the
-// thread knows that it initialises c.  Nothing here is written by k_mark: the
-// non-gas neighbours of a gas cell are interface cells (a liquid cell never
-// touches gas), and k_mark writes rows of new cells only.
-struct GasNbrs {
-  uint8_t tn[Q];
-  double4 vn[Q];
-};
+// All of a step's conversions (convert_all, fslbm_convert.hpp) in one launch;
+// most steps convert no cell or a few.  As three kernels of one thread per cell
+// and link they took 5.8 us of a step without conversions and 17 us with five
+// converted cells (101,565-cell tank, FP64); now 1.7 and about 8 us.
+// 512 groups of lanes (see convert_all) on an eighth of the compute units (the
+// workgroups wait for one another: see fslbm_barrier.hpp)
+constexpr int CBLOCK = 512;
+constexpr unsigned CGRID = 32;
 
-__device__ __forceinline__ void load_gas_nbrs(const ConvArgs& a, int c, GasNbrs& nb) {
-  const Grid& g = a.c.grid;
-  int x, y, z;
-  coords(g, c, x, y, z);
-#pragma unroll
-  for (int q = 1; q < Q; ++q) {
-    const int s = neighbor(g, x, y, z, CX[q], CY[q], CZ[q]);
-    const int sc = s >= 0 ? s : c;
-    nb.tn[q] = s >= 0 ? a.flags[sc] : (uint8_t)GAS;
-    nb.vn[q] = *reinterpret_cast<const double4*>(a.aux + 4 * (size_t)sc);
-  }
-}
-
-// f = f^eq of the mean collision density and velocity of the non-gas
-// neighbours, mass 0.
 template <class F>
-__device__ void init_new_from_gas(const ConvArgs& a, int c, const GasNbrs& nb) {
-  using R = typename F::R;
-  using S = typename F::S;
-  constexpr bool SH = F::shifted;
-  const Grid& g = a.c.grid;
-  double rs = 0.0, us0 = 0.0, us1 = 0.0, us2 = 0.0;
-  int cnt = 0;
-#pragma unroll
-  for (int q = 1; q < Q; ++q) {
-    if (nb.tn[q] == GAS || nb.tn[q] == SOLID) continue;
-    rs = rs + nb.vn[q].x;
-    us0 = us0 + nb.vn[q].y;
-    us1 = us1 + nb.vn[q].z;
-    us2 = us2 + nb.vn[q].w;
-    ++cnt;
-  }
-  const double rbar = rs / (double)cnt;
-  R ubar[3] = {(R)(us0 / (double)cnt), (R)(us1 / (double)cnt), (R)(us2 / (double)cnt)};
-  const R rs_store = SH ? (R)(rbar - 1.0) : (R)rbar;
-  const Consts<R>& k = pick_consts<R>(a.c);
-  R out[Q];
-  equilibrium_post<R, SH>(rs_store, ubar, k, a.c.incomp, a.c.stokes, out);
-  S* fo = reinterpret_cast<S*>(a.fout);
-#pragma unroll
-  for (int q = 0; q < Q; ++q) F::store(fo + (size_t)q * g.N + c, out[q], a.c.scale);
-  a.mass[c] = 0.0;
-  a.aux[4 * (size_t)c] = rbar;
-}
-
-// A new interface cell from liquid keeps its populations (of time t+1, written
-// by the sweep); m = rho.  The populations are loaded by the caller.
-template <class F>
-__device__ void init_new_from_liquid(const ConvArgs& a, int c, const typename F::R (&fl)[Q]) {
-  double r;
-  if (F::shifted) {
-    double s = 0.0;
-    for (int q = 0; q < Q; ++q) s = s + (double)fl[q];
-    r = 1.0 + s;
-  } else {
-    r = (double)fl[0];
-    for (int q = 1; q < Q; ++q) r = r + (double)fl[q];
-  }
-  a.mass[c] = r;
-  a.aux[4 * (size_t)c] = r;
-}
-
-// Mark of an E' cell in new_epoch: below every step stamp (>= 0) and the
-// initial -1, and distinct for every step.  E' cells are interface cells and
-// new_epoch's step stamps go to gas and liquid cells only.
-__device__ __forceinline__ int ep_stamp(int step) { return -2 - step; }
-
-// One thread per (converted cell, link): a cell's 18 neighbours are handled by
-// 18 threads, so the work of a step is not the longest serial chain of one
-// cell's new neighbours.  Which thread wins a new cell's epoch mark does not
-// change the result (its initialisation reads only pre-conversion classes).
-template <class F>
-__global__ __launch_bounds__(BLOCK) void k_mark(ConvArgs a) {
-  using R = typename F::R;
-  using S = typename F::S;
+__global__ __launch_bounds__(CBLOCK) void k_convert(ConvArgs a) {
+  GridBarrier grid(a.bar);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *a.bar_next = 0ull;
   const int nF = a.counters[C_F], nE = a.counters[C_E];
-  const Grid& g = a.c.grid;
-  const S* fo = reinterpret_cast<const S*>(a.fout);
-  // 18 N < 19 N < 2^32 (the lattice limit): the pair index fits in 32 unsigned bits
-  const unsigned total = (unsigned)(nF + nE) * (unsigned)(Q - 1);
-  for (unsigned i = blockIdx.x * BLOCK + threadIdx.x; i < total; i += gridDim.x * BLOCK) {
-    const int e = (int)(i / (unsigned)(Q - 1));
-    const int q = 1 + (int)(i - (unsigned)e * (unsigned)(Q - 1));
-    const int c = e < nF ? a.listF[e] : a.listE[e - nF];
-    int x, y, z;
-    coords(g, c, x, y, z);
-    const int s = neighbor(g, x, y, z, CX[q], CY[q], CZ[q]);
-    const uint8_t ts = s >= 0 ? a.flags[s] : (uint8_t)SOLID;
-    if (e < nF) {
-      // a gas neighbour: its initialisation data load with the claim
-      bool win = false;
-      GasNbrs nb;
-      if (ts == GAS) {
-        load_gas_nbrs(a, s, nb);
-        win = atomicExch(&a.new_epoch[s], a.step) != a.step;
-      }
-      wave_append(win, &a.counters[C_NI], a.listNI, s);
-      if (win) init_new_from_gas<F>(a, s, nb);
-    } else {
-      // E' = E minus N(F): every thread of the cell takes the same decision
-      bool protect = false;
-#pragma unroll
-      for (int p = 1; p < Q; ++p) {
-        const int t = neighbor(g, x, y, z, CX[p], CY[p], CZ[p]);
-        if (t >= 0 && a.f_epoch[t] == a.step) protect = true;
-      }
-      if (protect) continue;
-      if (q == 1) a.new_epoch[c] = ep_stamp(a.step);
-      wave_append(q == 1, &a.counters[C_EP], a.listEP, c);
-      // a liquid neighbour: its populations load with the claim
-      bool win = false;
-      R fl[Q];
-      if (ts == LIQ) {
-#pragma unroll
-        for (int p = 0; p < Q; ++p) fl[p] = F::load(fo + (size_t)p * g.N + s, a.c.inv_scale);
-        win = atomicExch(&a.new_epoch[s], a.step) != a.step;
-      }
-      wave_append(win, &a.counters[C_NL], a.listNL, s);
-      if (win) init_new_from_liquid<F>(a, s, fl);
-    }
-  }
-}
-
-// Whether cell t is an interface cell after this step's conversions: a new
-// interface cell, or an interface cell of time t that neither filled nor is in
-// E'.  Three loads, no branch, so that a caller's 18 neighbours load in one
-// batch.
-__device__ __forceinline__ bool iface_after(const ConvArgs& a, int t) {
-  const int ne = a.new_epoch[t];
-  const int fe = a.f_epoch[t];
-  const uint8_t fl = a.flags[t];
-  return (ne == a.step) | ((fl == IFACE) & (fe != a.step) & (ne != ep_stamp(a.step)));
-}
-
-// One thread per (converted cell, link), as in k_mark: every thread of a cell
-// counts its eligible neighbours; the link-1 thread takes the excess (a filled
-// cell's mass minus its density, an emptied cell's mass), divides it (or hands
-// it to the reservoir) and marks the cell, each thread lists its own receiver.
-__global__ __launch_bounds__(BLOCK) void k_share(ConvArgs a) {
-  const int nF = a.counters[C_F], nEP = a.counters[C_EP];
-  const Grid& g = a.c.grid;
-  // 18 N < 19 N < 2^32 (the lattice limit): the pair index fits in 32 unsigned bits
-  const unsigned total = (unsigned)(nF + nEP) * (unsigned)(Q - 1);
-  for (unsigned i = blockIdx.x * BLOCK + threadIdx.x; i < total; i += gridDim.x * BLOCK) {
-    const int e = (int)(i / (unsigned)(Q - 1));
-    const int q = 1 + (int)(i - (unsigned)e * (unsigned)(Q - 1));
-    const bool filled = e < nF;
-    const int c = filled ? a.listF[e] : a.listEP[e - nF];
-    int x, y, z;
-    coords(g, c, x, y, z);
-    int n_elig = 0;
-    bool recv = false;
-#pragma unroll
-    for (int p = 1; p < Q; ++p) {
-      const int t = neighbor(g, x, y, z, CX[p], CY[p], CZ[p]);
-      const bool el = (t >= 0) & iface_after(a, t >= 0 ? t : c);
-      n_elig += el ? 1 : 0;
-      if (p == q) recv = el;
-    }
-    if (q == 1) {
-      const double ex = filled ? a.mass[c] - a.aux[4 * (size_t)c] : a.mass[c];
-      if (n_elig == 0) {
-        atomicAdd(a.reservoir, ex);
-        if (filled) a.mass[c] = ex;
-      } else {
-        a.mass[c] = ex / (double)n_elig;
-        a.conv_epoch[c] = a.step;
-      }
-    }
-    if (!recv) continue;
-    const int s = neighbor(g, x, y, z, CX[q], CY[q], CZ[q]);
-    wave_append(atomicExch(&a.recv_epoch[s], a.step) != a.step, &a.counters[C_R], a.listR, s);
-  }
-}
-
-// Receivers (first nR threads) and the new cell classes (the rest; with the
-// interface kernel first, the new interface cells also join the next list).
-__global__ __launch_bounds__(BLOCK) void k_gather(ConvArgs a) {
-  const int nR = a.counters[C_R];
-  const int nF = a.counters[C_F], nEP = a.counters[C_EP], nNI = a.counters[C_NI], nNL = a.counters[C_NL];
-  const int tot = nR + nF + nEP + nNI + nNL;
-  const Grid& g = a.c.grid;
-  for (int i = blockIdx.x * BLOCK + threadIdx.x; i < tot; i += gridDim.x * BLOCK) {
-    if (i >= nR) {
-      int j = i - nR, cell;
-      uint8_t cls;
-      if (j < nF) {
-        cell = a.listF[j];
-        cls = LIQ;
-      } else if ((j -= nF) < nEP) {
-        cell = a.listEP[j];
-        cls = GAS;
-      } else if ((j -= nEP) < nNI) {
-        cell = a.listNI[j];
-        cls = IFACE;
-      } else {
-        cell = a.listNL[j - nNI];
-        cls = IFACE;
-      }
-      a.flags[cell] = cls;
-      if (a.order) {
-        // a new interface cell joins the list of the next step
-        const bool join = cls == IFACE;
-        const int pos = wave_append_at(join, &a.counters_next[C_I], a.listI, cell);
-        if (join) a.islot[cell] = pos;
-      }
-      continue;
-    }
-    const int r = a.listR[i];
-    int x, y, z;
-    coords(g, r, x, y, z);
-    double m = a.mass[r];
-    // marks and masses of all neighbours in one batch of loads, then the sum
-    // in link order (a neighbour beyond a wall reads the cell's own entries)
-    int ep[Q];
-    double mn[Q];
-#pragma unroll
-    for (int q = 1; q < Q; ++q) {
-      const int s = neighbor(g, x, y, z, CX[q], CY[q], CZ[q]);
-      const int sc = s >= 0 ? s : r;
-      ep[q] = s >= 0 ? a.conv_epoch[sc] : -1;
-      mn[q] = a.mass[sc];
-    }
-#pragma unroll
-    for (int q = 1; q < Q; ++q)
-      if (ep[q] == a.step) m = m + mn[q];
-    a.mass[r] = m;
-    a.phi_out[r] = m / a.aux[4 * (size_t)r];
-  }
+  if (nF + nE > 0) convert_all<F, CBLOCK>(a, a.step, nF, nE, grid);
 }
 
 // The interface cells of the current classes into list and islot (cell -> list
@@ -1000,7 +772,6 @@ __global__ __launch_bounds__(BLOCK) void k_stats(StatArgs a) {
 
 // ------------------------------------------------------------ launchers
 static inline unsigned blocks_for(size_t n) { return (unsigned)((n + BLOCK - 1) / BLOCK); }
-static constexpr unsigned LIST_GRID = 512;
 static constexpr unsigned IFACE_GRID = 8192;
 
 template <class F, int RULE, bool REC, bool EXTRA>
@@ -1047,9 +818,7 @@ static void iface_form(const StepLaunch& L, int rule) {
 template <class F>
 static void convert_form(const StepLaunch& L) {
   hipStream_t st = (hipStream_t)L.stream;
-  k_mark<F><<<LIST_GRID, BLOCK, 0, st>>>(L.conv);
-  k_share<<<LIST_GRID, BLOCK, 0, st>>>(L.conv);
-  k_gather<<<LIST_GRID, BLOCK, 0, st>>>(L.conv);
+  k_convert<F><<<CGRID, CBLOCK, 0, st>>>(L.conv);
 }
 
 // Liquid cells next to solid cells (the wall list; interface cells there are

@@ -71,4 +71,14 @@ __device__ __forceinline__ double ddot(const int (&d)[3], const double (&v)[3]) 
   return ((double)d[0] * v[0] + (double)d[1] * v[1]) + (double)d[2] * v[2];
 }
 
+// even equilibrium e+ of a link with c.u = cu and weight wq (Eq. eqEven), the
+// operations of e_plus<q>
+template <class R>
+__device__ __forceinline__ R e_plus_w(R wq, R cu, R rho_s, R rho0, bool incomp, bool stokes, R usq) {
+  if (stokes) return wq * rho_s;
+  R nl = R(4.5) * (cu * cu) - R(1.5) * usq;
+  if (!incomp) nl = rho0 * nl;
+  return wq * (rho_s + nl);
+}
+
 }  // namespace fslbm
