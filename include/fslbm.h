@@ -157,7 +157,8 @@ typedef struct {
 /* Bytes of workspace a context from fslbm_init with these parameters needs
  * (in the FP32 and FP64 forms including a cell -> list-entry map and a
  * list-ordered population buffer of N/8 entries, at least 32768, for the
- * interface-first step of fslbm_step). */
+ * interface-first step of fslbm_step; up to 32,768 cells also the interface list
+ * of the one-launch form). */
 fslbm_status fslbm_workspace_size(const fslbm_params* p, size_t* bytes);
 
 /* Validate parameters and buffers, check the cell classes on the device (every
@@ -220,7 +221,12 @@ fslbm_status fslbm_set_state(fslbm_ctx* c, const double* f, const double* mass, 
  * are the same bits as with the interface kernel after the sweep.  The
  * environment variable FSLBM_REORDER at init (0 / 1) selects either order for
  * the FP32 and FP64 forms; FP16 storage always runs the interface kernel
- * after the sweep.  The classes change
+ * after the sweep.  On lattices of up to 32,768 cells the plain step of the
+ * FP32 and FP64 forms runs in one launch of up to 256 steps (without the wait
+ * above), unless fslbm_timing records sweeps or one of the environment
+ * variables above, FSLBM_IFACE_QUAD, FSLBM_FP16_PAIRS or FSLBM_RCAP chooses
+ * between the kernels of the step-by-step form at init (FSLBM_RESIDENT=0:
+ * never); the results are the same bits.  The classes change
  * only through the steps: a caller that writes the flags buffer between steps
  * calls fslbm_set_state or fslbm_set_equilibrium afterwards, which also make
  * the next step measure the extent again and rebuild the interface list.

@@ -3,12 +3,13 @@ from __future__ import annotations
 
 import os
 import subprocess
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libfslbm.so")
-SOURCES = ["fslbm_sweep.hip", "fslbm_kernels.hip", "fslbm_iface4.hip", "fslbm_adjoint.hip", "fslbm_capi.hip"]
+SOURCES = ["fslbm_sweep.hip", "fslbm_kernels.hip", "fslbm_iface4.hip", "fslbm_resident.hip", "fslbm_adjoint.hip", "fslbm_capi.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # -ffp-contract=off: no FMA contraction, so the FP64 form reproduces the
@@ -20,16 +21,18 @@ FLAGS = ["-std=c++17", "-O3", "--offload-arch=gfx950", "-fPIC", "-ffp-contract=o
 
 
 def build(verbose: bool = False) -> str:
-    objs = []
     bdir = os.path.join(HERE, "_build")
     os.makedirs(bdir, exist_ok=True)
-    for src in SOURCES:
-        obj = os.path.join(bdir, src.replace(".hip", ".o"))
+    objs = [os.path.join(bdir, src.replace(".hip", ".o")) for src in SOURCES]
+
+    def compile_one(src, obj):
         cmd = [HIPCC, *FLAGS, "-I", os.path.join(ROOT, "include"), "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.run(cmd, check=True)
-        objs.append(obj)
+
+    with ThreadPoolExecutor(max_workers=4) as pool:  # one compiler each
+        list(pool.map(compile_one, SOURCES, objs))
     tmp = LIB_PATH + ".tmp"
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], check=True)
     os.replace(tmp, LIB_PATH)

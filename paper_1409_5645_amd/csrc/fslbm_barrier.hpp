@@ -16,8 +16,9 @@ __device__ __forceinline__ void drain_stores() { asm volatile("s_waitcnt vmcnt(0
 // Barrier of the whole grid on one counter (zero at launch): the low word
 // counts arrivals, the upper two 16-bit fields the flags raised at even and at
 // odd barriers (a workgroup that is ahead can be at most one barrier on, so it
-// cannot disturb the field that a late one still reads).  Returns whether any
-// workgroup raised its flag.
+// cannot disturb the field that a late one still reads; RESIDENT_STEPS steps of
+// at most 64 workgroups fit a field).  Returns whether any workgroup raised its
+// flag.
 struct GridBarrier {
   unsigned long long* p;
   unsigned target, index, seen[2];

@@ -39,6 +39,9 @@ struct fslbm_ctx {
   int rcap = 0;
   bool reorder = false;
   bool list_ok = false;
+  // runs of steps in one launch (small lattices): the interface list of that
+  // kernel, cell -> entry, its length
+  int32_t *res_list = nullptr, *res_slot = nullptr, *res_len = nullptr;
   // barrier words of the kernels whose workgroups meet: a launch counts in one
   // and zeroes the other for the next
   unsigned long long* bars = nullptr;
@@ -92,7 +95,8 @@ size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 size_t storage_bytes(int precision) { return precision == FSLBM_FP64 ? 8 : (precision == FSLBM_FP32 ? 4 : 2); }
 
 struct Layout {
-  size_t aux, epochs[4], lists[7], counters, scalars, extent, wall_t, kappa, khf, islot, rbuf, rcap, bars, total;
+  size_t aux, epochs[4], lists[7], counters, scalars, extent, wall_t, kappa, khf, islot, rbuf, rcap, res_list, res_slot, res_len,
+      bars, total;
 };
 
 // Entries of the list-ordered population buffer of the interface-first step:
@@ -120,7 +124,8 @@ void wall_table(const fslbm_params& p, double out[6 * Q]) {
 // kappa: with surface tension, one Laplace-pressure correction per listed cell;
 // hf: with surface tension and plic = 2, the height-function kappa per cell;
 // reorder: room for the interface-first step (cell -> list entry, 19
-// populations of s bytes per list entry)
+// populations of s bytes per list entry); lattices of up to RESIDENT_CELLS
+// also (not in the FP16 form) have the list of the resident step
 Layout layout(size_t N, bool kappa, bool hf, size_t s, bool reorder) {
   Layout L{};
   size_t o = 0;
@@ -151,6 +156,13 @@ Layout layout(size_t N, bool kappa, bool hf, size_t s, bool reorder) {
   if (reorder) o = align_up(o + 4 * N);
   L.rbuf = o;
   if (reorder) o = align_up(o + (size_t)Q * s * L.rcap);
+  const bool small = N <= (size_t)RESIDENT_CELLS && s != storage_bytes(FSLBM_FP16S);
+  L.res_list = o;
+  if (small) o = align_up(o + 8 * N);
+  L.res_slot = o;
+  if (small) o = align_up(o + 4 * N);
+  L.res_len = o;
+  if (small) o = align_up(o + NCOUNT * sizeof(int32_t));
   L.bars = o;
   o = align_up(o + 2 * ALIGN);
   L.total = o;
@@ -328,6 +340,17 @@ fslbm_status init_impl(const fslbm_params* p, const fslbm_buffers* b, void* work
     c->reorder = p->precision == FSLBM_FP32;
     if (const char* e = std::getenv("FSLBM_REORDER")) c->reorder = std::atoi(e) != 0 && p->precision != FSLBM_FP16S;
     if (const char* e = std::getenv("FSLBM_RCAP")) c->rcap = std::max(0, std::min(c->rcap, std::atoi(e)));
+  }
+  // The resident step, unless the environment chooses the layout or order of
+  // the kernels of the step-by-step form (FSLBM_RESIDENT=0: never)
+  bool resident = N <= (size_t)RESIDENT_CELLS && p->precision != FSLBM_FP16S;
+  for (const char* name : {"FSLBM_REORDER", "FSLBM_RCAP", "FSLBM_IFACE_QUAD", "FSLBM_FP16_PAIRS", "FSLBM_EXTENT_EVERY"})
+    if (std::getenv(name)) resident = false;
+  if (const char* e = std::getenv("FSLBM_RESIDENT")) resident = resident && std::atoi(e) != 0;
+  if (resident) {
+    c->res_list = (int32_t*)(w + L.res_list);
+    c->res_slot = (int32_t*)(w + L.res_slot);
+    c->res_len = (int32_t*)(w + L.res_len);
   }
   c->bars = (unsigned long long*)(w + L.bars);
   {
@@ -669,6 +692,38 @@ void step_args(const fslbm_ctx* c, StepLaunch& L) {
 // surface take the step off the plain kernels.
 bool extra_step(const Common& m) { return m.moving || m.sigma != 0.0 || m.plic || m.solid || m.surface; }
 
+// m plain steps in one launch.
+hipError_t resident_steps(fslbm_ctx* c, int m, int32_t rule) {
+  StepLaunch L{};
+  step_args(c, L);
+  ResidentArgs r{};
+  for (int k = 0; k < 2; ++k) {
+    SweepArgs& s = r.sweep[k] = L.sweep;
+    ConvArgs& v = r.conv[k] = L.conv;
+    const int in = k ? 1 - c->cur : c->cur;
+    s.fin = c->f[in];
+    s.fout = v.fout = c->f[1 - in];
+    s.phi_in = c->phi[in];
+    s.phi_out = v.phi_out = c->phi[1 - in];
+    s.counters = v.counters = c->counters + ((c->step + k) & 1) * NCOUNT;
+    s.counters_next = c->counters + ((c->step + k + 1) & 1) * NCOUNT;
+    v.order = 1;
+    v.listI = c->res_list;
+    v.islot = c->res_slot;
+    v.counters_next = c->res_len;
+  }
+  r.list = c->res_list;
+  r.islot = c->res_slot;
+  r.len = c->res_len;
+  r.bar = L.conv.bar;
+  r.bar_next = L.conv.bar_next;
+  r.step = c->step;
+  r.n = m;
+  const hipError_t e = launch_resident(r, c->p.precision, rule, (void*)c->stream);
+  if (e == hipSuccess) c->bar_flip = 1 - c->bar_flip;
+  return e;
+}
+
 }  // namespace
 
 extern "C" {
@@ -685,7 +740,21 @@ fslbm_status fslbm_step(fslbm_ctx* c, int32_t n, int32_t rule) {
     c->last_error = "solid cells present: set their wall table with fslbm_set_walls first";
     return FSLBM_E_INVALID;
   }
-  for (int32_t i = 0; i < n; ++i) {
+  const bool resident = c->res_list && !c->timing && !extra_step(c->com);
+  int32_t m = 1;  // steps of one pass of the loop
+  for (int32_t i = 0; i < n; i += m) {
+    if (resident) {
+      // up to the next health check
+      m = std::min<int32_t>(n - i, RESIDENT_STEPS);
+      if (c->check_every > 0) m = std::min<int32_t>(m, c->check_every - c->step % c->check_every);
+      HIPCHK(c, resident_steps(c, m, rule), "resident launch");
+      c->list_ok = false;
+      if (m & 1) c->cur = 1 - c->cur;
+      c->step += m;
+      const fslbm_status hs = check_due(c);
+      if (hs != FSLBM_OK) return hs;
+      continue;
+    }
     StepLaunch L{};
     step_args(c, L);
     SweepArgs& s = L.sweep;

@@ -137,6 +137,29 @@ struct StepLaunch {
   void* stream;
 };
 
+// A run of n plain steps of a small lattice in one launch (fslbm_resident.hip).
+// sweep[k], conv[k]: arguments of the even and the odd steps of the run (the
+// buffers and counter sets alternate; the step stamp is step + t); conv's
+// order, listI, islot and counters_next name the kernel's own list.
+struct ResidentArgs {
+  SweepArgs sweep[2];
+  ConvArgs conv[2];
+  int32_t* list;   // interface cells, 2 N entries
+  int32_t* islot;  // cell -> its entry
+  int32_t* len;    // NCOUNT values, [C_I] the length of the list
+  unsigned long long* bar;       // barrier word, zero
+  unsigned long long* bar_next;  // barrier word of the next launch (zeroed by this one)
+  int step, n;
+};
+static_assert(sizeof(ResidentArgs) <= 4096, "kernel arguments");
+// Largest lattice: up to here the launches cost more than the step's work
+// (us a step without conversions, kernels against resident: 1,280 cells FP32
+// 17.4 / 3.8, 3,072 FP64 19.4 / 6.2, 12,000 FP64 20.2 / 9.9, 30,000 FP32 19.4 /
+// 10.7; with ten conversions a step 30,000 FP32 30.3 / 29.2, FP64 33.0 / 33.8;
+// 61,440 FP64 without conversions 22.1 / 25.8).  Steps per launch: see
+// GridBarrier.
+constexpr int RESIDENT_CELLS = 32768;
+constexpr int RESIDENT_STEPS = 256;
 // Converted cells of a step that one workgroup takes (convert_all): its 16
 // groups of lanes do up to about eight cells and their neighbours in one or
 // two rounds.  101,565-cell tank with about 5 conversions a step (FP32): 29.0 us
@@ -228,6 +251,7 @@ hipError_t launch_iface(const StepLaunch& L, int precision, int rule);
 hipError_t launch_iface4(const StepLaunch& L, int precision, int rule);  // fslbm_iface4.hip
 hipError_t launch_curvature(const StepLaunch& L);  // one or (plic = 2) two list kernels
 hipError_t launch_convert(const StepLaunch& L, int precision);
+hipError_t launch_resident(const ResidentArgs& r, int precision, int rule, void* stream);
 // interface cells of the current classes -> list, islot, *counter (a step with
 // the interface kernel first after a new state)
 hipError_t launch_list_append(const uint8_t* flags, const Grid& g, int32_t* counter, int32_t* list, int32_t* islot,
