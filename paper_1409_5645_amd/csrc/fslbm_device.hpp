@@ -190,7 +190,8 @@ __device__ __forceinline__ void collide(R f[Q], const Consts<R>& k, bool incomp,
 // that saves issue slots is taken here and only here).  With SCALED, f holds
 // populations in units of 1/sc (the FP16 storage scale), which the collision is
 // linear in except for the quadratic equilibrium term and the velocity; sc is
-// folded into those constants instead of rescaling all 19 values.
+// folded into those constants instead of rescaling all 19 values (products with a
+// power of two are exact, so where they go does not change the result).
 template <bool SHIFTED, bool SCALED>
 __device__ __forceinline__ void collide_f32_scaled(float f[Q], const Consts<float>& k, bool incomp, bool stokes,
                                                    float sc, float isc, float& rho_s, float u[3]) {
@@ -224,11 +225,11 @@ __device__ __forceinline__ void collide_f32_scaled(float f[Q], const Consts<floa
   {                                                                       \
     const float cu = cdot<q>(u);                                          \
     const float cue = cdot<q>(ueq);                                       \
-    const float em = float(W3D[q]) * (incomp && !SCALED ? cue : r0s * cue); \
+    const float em = incomp ? (SCALED ? float(W3D[q]) * sc : float(W3D[q])) * cue : float(W3D[q]) * (r0s * cue); \
     const float ep = ep_of(cu, q, q <= 6 ? 1 : 2);                        \
     const float a = f[q], b = f[q + 1];                                   \
-    const float np = 0.5f * (a + b) - ep;                                 \
-    const float nm = 0.5f * (a - b) - em;                                 \
+    const float np = __builtin_fmaf(0.5f, a + b, -ep);                    \
+    const float nm = __builtin_fmaf(0.5f, a - b, -em);                    \
     const float lpn = k.lp * np;                                          \
     f[q] = __builtin_fmaf(k.lm, nm, a + lpn);                             \
     f[q + 1] = __builtin_fmaf(-k.lm, nm, b + lpn);                        \

@@ -12,7 +12,7 @@ constexpr int BLOCK = 256;
 // Stream/collide sweep over liquid cells, one cell per lane; a block covers a
 // chunk of one lattice row, so the row, its y and z and the source rows of
 // every link are uniform (scalar) values.  Interface cells are appended to the
-// interface list (one atomic per wavefront) and updated by the interface
+// interface list (one atomic per block) and updated by the interface
 // kernel.  A wavefront without liquid cells exits; in one with liquid cells
 // every lane of the row (but solid cells) pulls, collides and stores, so that
 // its stores cover whole cache lines: a partly written line costs the memory
@@ -57,22 +57,17 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(SweepArgs a) {
   const unsigned rbase = (unsigned)row * (unsigned)g.nx;
   const uint8_t t = x < g.nx ? a.flags[rbase + x] : GAS;
   const int lane = (int)threadIdx.x & 63;
+  const unsigned long long b = __ballot(t == IFACE);
   if constexpr (!ORDER1) {
-    // interface cells -> list (wavefront-aggregated append)
-    const unsigned long long b = __ballot(t == IFACE);
-    if (b) {
-      const int leader = __ffsll((long long)b) - 1;
-      int base = 0;
-      if (lane == leader) base = atomicAdd(&a.counters[C_I], __popcll(b));
-      base = __shfl(base, leader);
-      if (t == IFACE) a.listI[base + __popcll(b & ((1ull << lane) - 1ull))] = (int)(rbase + x);
-    }
+    // interface cells -> list
+    const int pos = block_reserve<BLOCK / 64>(__popcll(b), &a.counters[C_I]) + __popcll(b & ((1ull << lane) - 1ull));
+    if (t == IFACE) a.listI[pos] = (int)(rbase + x);
   }
   // with the interface kernel first, a wavefront without liquid cells that
   // holds interface cells pulls nothing: it only stores their populations
   // from the list buffer
   const bool wliq = __ballot(t == LIQ) != 0ull;
-  if (!wliq && (!ORDER1 || __ballot(t == IFACE) == 0ull)) return;
+  if (!wliq && (!ORDER1 || b == 0ull)) return;
   if (x >= g.nx || t == SOLID) return;
 
   // source rows (element offsets) of the nine (c_y, c_z) combinations
@@ -149,7 +144,7 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(SweepArgs a) {
     int oslot = -1;
     if (it) oslot = a.islot[rbase + x];
     const int pos = wave_append_at(it, &a.counters_next[C_I], a.listI, (int)(rbase + x));
-    if (__ballot(it) != 0ull) a.islot[rbase + x] = pos;
+    if (b != 0ull) a.islot[rbase + x] = pos;
     const bool keep = it && (unsigned)oslot >= (unsigned)a.rcap;
     if (it && !keep) {
       const S* __restrict__ rb = reinterpret_cast<const S*>(a.rbuf) + oslot;
@@ -276,18 +271,13 @@ __global__ __launch_bounds__(BLOCK) void k_sweep_h2(SweepArgs a) {
   const uint16_t fl2 = valid ? *reinterpret_cast<const uint16_t*>(a.flags + rbase + xl) : (uint16_t)0;
   const uint8_t tt[2] = {(uint8_t)(fl2 & 0xffu), (uint8_t)(fl2 >> 8)};
   const int lane = (int)threadIdx.x & 63;
-  // interface cells -> list (wavefront-aggregated append, one cell of the pair at a time)
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const unsigned long long b = __ballot(tt[j] == IFACE);
-    if (b) {
-      const int leader = __ffsll((long long)b) - 1;
-      int base = 0;
-      if (lane == leader) base = atomicAdd(&a.counters[C_I], __popcll(b));
-      base = __shfl(base, leader);
-      if (tt[j] == IFACE) a.listI[base + __popcll(b & ((1ull << lane) - 1ull))] = (int)rbase + x0 + j;
-    }
-  }
+  // interface cells -> list, the first cells of the wavefront's pairs, then the second ones
+  const unsigned long long b0 = __ballot(tt[0] == IFACE), b1 = __ballot(tt[1] == IFACE);
+  const int n0 = __popcll(b0);
+  const int pos = block_reserve<BLOCK / 64>(n0 + __popcll(b1), &a.counters[C_I]);
+  const unsigned long long below = (1ull << lane) - 1ull;
+  if (tt[0] == IFACE) a.listI[pos + __popcll(b0 & below)] = (int)rbase + x0;
+  if (tt[1] == IFACE) a.listI[pos + n0 + __popcll(b1 & below)] = (int)rbase + x0 + 1;
   const bool liq = tt[0] == LIQ || tt[1] == LIQ;
   if (__ballot(liq) == 0) return;  // lanes exchange data below: whole wavefronts only
 
