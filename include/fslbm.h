@@ -158,7 +158,9 @@ typedef struct {
  * (in the FP32 and FP64 forms including a cell -> list-entry map and a
  * list-ordered population buffer of N/8 entries, at least 32768, for the
  * interface-first step of fslbm_step; up to 32,768 cells also the interface list
- * of the one-launch form). */
+ * of the one-launch form; where population buffers are 300 MB to 17 GB each and
+ * y is not periodic, no wall moves and the equilibrium is the incompressible one
+ * with its quadratic term, a third population buffer for the two-step kernel). */
 fslbm_status fslbm_workspace_size(const fslbm_params* p, size_t* bytes);
 
 /* Validate parameters and buffers, check the cell classes on the device (every
@@ -226,7 +228,13 @@ fslbm_status fslbm_set_state(fslbm_ctx* c, const double* f, const double* mass, 
  * above), unless fslbm_timing records sweeps or one of the environment
  * variables above, FSLBM_IFACE_QUAD, FSLBM_FP16_PAIRS or FSLBM_RCAP chooses
  * between the kernels of the step-by-step form at init (FSLBM_RESIDENT=0:
- * never); the results are the same bits.  The classes change
+ * never); the results are the same bits.  Where the workspace holds a third
+ * population buffer (fslbm_workspace_size), two steps of a call are taken at
+ * once for the rows at the low y end that are liquid throughout, as the extent
+ * (measured every 8 steps there) shows, unless fslbm_timing records sweeps or a
+ * health check falls between the two (FSLBM_DEEP=0 at init: never); again the
+ * same bits, and the current populations may then lie in any of the three
+ * buffers.  The classes change
  * only through the steps: a caller that writes the flags buffer between steps
  * calls fslbm_set_state or fslbm_set_equilibrium afterwards, which also make
  * the next step measure the extent again and rebuild the interface list.

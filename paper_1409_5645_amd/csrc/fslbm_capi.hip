@@ -18,12 +18,14 @@ struct fslbm_ctx {
   fslbm_params p;
   Common com;
   double thr_hi, thr_lo;
-  void* f[2];
+  void* f[3] = {nullptr, nullptr, nullptr};  // the third in the workspace, where the two-step kernel may run
+  int nf = 2;
+  int fcur = 0;         // index of the population buffer holding time t
   uint8_t* flags;
   double* mass;
   double* phi[2];
   hipStream_t stream;
-  int cur = 0;          // index of the buffers holding time t
+  int cur = 0;          // index of the fill buffer holding time t
   int step = 0;         // steps done (also the epoch stamp of the next step)
   // workspace carve-out
   double* aux;  // [N][4] collision density and velocity of interface cells
@@ -78,10 +80,11 @@ struct fslbm_ctx {
   // neighbours of filled ones).  Off (every row) for fslbm_init_static.
   int ext_every = 0;
   int32_t* ext_dev = nullptr;        // workspace: the kernel's output
-  int32_t* ext_host = nullptr;       // pinned: two slots of 4 values
+  int32_t* ext_host = nullptr;       // pinned: two slots of EXT_VALUES values
   hipEvent_t ext_ev[2] = {nullptr, nullptr};
   int ext_step[2] = {-1, -1};        // step whose flags each slot describes
   int ext_pending = -1, ext_valid = -1;
+  bool deep = false;                 // two steps at once below the surface (needs the third buffer)
   double u_max2 = 0.16; // square of the |u| bound of the health check
 };
 
@@ -96,7 +99,7 @@ size_t storage_bytes(int precision) { return precision == FSLBM_FP64 ? 8 : (prec
 
 struct Layout {
   size_t aux, epochs[4], lists[7], counters, scalars, extent, wall_t, kappa, khf, islot, rbuf, rcap, res_list, res_slot, res_len,
-      bars, total;
+      bars, third, total;
 };
 
 // Entries of the list-ordered population buffer of the interface-first step:
@@ -125,8 +128,9 @@ void wall_table(const fslbm_params& p, double out[6 * Q]) {
 // hf: with surface tension and plic = 2, the height-function kappa per cell;
 // reorder: room for the interface-first step (cell -> list entry, 19
 // populations of s bytes per list entry); lattices of up to RESIDENT_CELLS
-// also (not in the FP16 form) have the list of the resident step
-Layout layout(size_t N, bool kappa, bool hf, size_t s, bool reorder) {
+// also (not in the FP16 form) have the list of the resident step; third: a
+// third population buffer, for the two-step kernel
+Layout layout(size_t N, bool kappa, bool hf, size_t s, bool reorder, bool third) {
   Layout L{};
   size_t o = 0;
   L.aux = o;
@@ -165,6 +169,8 @@ Layout layout(size_t N, bool kappa, bool hf, size_t s, bool reorder) {
   if (small) o = align_up(o + NCOUNT * sizeof(int32_t));
   L.bars = o;
   o = align_up(o + 2 * ALIGN);
+  L.third = o;
+  if (third) o = align_up(o + (size_t)Q * s * N);
   L.total = o;
   return L;
 }
@@ -194,6 +200,17 @@ fslbm_status check_params(const fslbm_params* p, std::string& why) {
   for (int a = 0; a < 3; ++a)
     if (!std::isfinite(p->g[a])) { why = "g must be finite"; return FSLBM_E_INVALID; }
   return FSLBM_OK;
+}
+
+// Whether the two-step kernel (fslbm_deep.hip) may run on such a lattice: a
+// context then has a third population buffer in its workspace.
+bool deep_lattice(const fslbm_params& p) {
+  if (p.periodic[1] || !p.incompressible || p.stokes) return false;
+  for (int f = 0; f < 6; ++f)
+    for (int a = 0; a < 3; ++a)
+      if (!p.periodic[f / 2] && p.wall_u[f][a] != 0.0) return false;
+  const double bytes = (double)Q * p.nx * p.ny * p.nz * storage_bytes(p.precision);
+  return p.precision != FSLBM_FP16S && bytes >= DEEP_MIN_BYTES && bytes <= DEEP_MAX_BYTES;
 }
 
 fslbm_status dev_fail(fslbm_ctx* c, hipError_t e, const char* what) {
@@ -276,7 +293,7 @@ fslbm_status fslbm_workspace_size(const fslbm_params* p, size_t* bytes) {
   if (s != FSLBM_OK) { g_init_error = why; return s; }
   if (!bytes) { g_init_error = "bytes is NULL"; return FSLBM_E_INVALID; }
   *bytes = layout((size_t)p->nx * p->ny * p->nz, p->sigma != 0.0, p->plic == 2, storage_bytes(p->precision),
-                  p->precision != FSLBM_FP16S).total;
+                  p->precision != FSLBM_FP16S, deep_lattice(*p)).total;
   return FSLBM_OK;
 }
 
@@ -287,13 +304,13 @@ namespace {
 // fslbm_init with the workspace given separately (the caller's buffer, or the
 // library's static array for fslbm_init_static); parameters already checked.
 fslbm_status init_impl(const fslbm_params* p, const fslbm_buffers* b, void* workspace, size_t workspace_bytes,
-                       bool reorder, fslbm_ctx** out) {
+                       bool reorder, bool third, fslbm_ctx** out) {
   if (!b->f[0] || !b->f[1] || !b->flags || !b->mass || !b->phi[0] || !b->phi[1] || !workspace) {
     g_init_error = "a device buffer is NULL";
     return FSLBM_E_INVALID;
   }
   const size_t N = (size_t)p->nx * p->ny * p->nz;
-  const Layout L = layout(N, p->sigma != 0.0, p->plic == 2, storage_bytes(p->precision), reorder);
+  const Layout L = layout(N, p->sigma != 0.0, p->plic == 2, storage_bytes(p->precision), reorder, third);
   if (workspace_bytes < L.total) { g_init_error = "workspace too small"; return FSLBM_E_INVALID; }
   if (((uintptr_t)workspace) % ALIGN) { g_init_error = "workspace not 256-byte aligned"; return FSLBM_E_INVALID; }
 
@@ -303,6 +320,10 @@ fslbm_status init_impl(const fslbm_params* p, const fslbm_buffers* b, void* work
   make_constants(*p, c->com, c->thr_hi, c->thr_lo);
   c->f[0] = b->f[0];
   c->f[1] = b->f[1];
+  if (third) {
+    c->f[2] = (char*)workspace + L.third;
+    c->nf = 3;
+  }
   c->flags = b->flags;
   c->mass = b->mass;
   c->phi[0] = b->phi[0];
@@ -411,13 +432,17 @@ fslbm_status fslbm_init(const fslbm_params* p, const fslbm_buffers* b, fslbm_ctx
   if (s != FSLBM_OK) { g_init_error = why; return s; }
   if (!b || !out) { g_init_error = "buffers or out is NULL"; return FSLBM_E_INVALID; }
   // the interface-first buffers: FP32 and FP64 forms (FP16 keeps the other order)
-  s = init_impl(p, b, b->workspace, b->workspace_bytes, p->precision != FSLBM_FP16S, out);
+  s = init_impl(p, b, b->workspace, b->workspace_bytes, p->precision != FSLBM_FP16S, deep_lattice(*p), out);
   if (s != FSLBM_OK) return s;
   fslbm_ctx* c = *out;
-  c->ext_every = 16;
+  // the two-step kernel's rows shrink by a row for every step since the
+  // measurement: measured twice as often there
+  c->deep = c->nf == 3;
+  if (const char* e = std::getenv("FSLBM_DEEP")) c->deep = c->deep && std::atoi(e) != 0;
+  c->ext_every = c->deep ? 8 : 16;
   if (const char* e = std::getenv("FSLBM_EXTENT_EVERY")) c->ext_every = std::max(0, std::atoi(e));
   if (c->ext_every > 0) {
-    hipError_t e = hipHostMalloc((void**)&c->ext_host, 8 * sizeof(int32_t), hipHostMallocDefault);
+    hipError_t e = hipHostMalloc((void**)&c->ext_host, 2 * EXT_VALUES * sizeof(int32_t), hipHostMallocDefault);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ext_ev[0], hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ext_ev[1], hipEventDisableTiming);
     if (e != hipSuccess) {
@@ -435,7 +460,7 @@ fslbm_status fslbm_init_static(const fslbm_params* p, const fslbm_buffers* b, fs
   if (s != FSLBM_OK) { g_init_error = why; return s; }
   if (!b || !out) { g_init_error = "buffers or out is NULL"; return FSLBM_E_INVALID; }
   const size_t need =
-      layout((size_t)p->nx * p->ny * p->nz, p->sigma != 0.0, p->plic == 2, storage_bytes(p->precision), false).total;
+      layout((size_t)p->nx * p->ny * p->nz, p->sigma != 0.0, p->plic == 2, storage_bytes(p->precision), false, false).total;
   if (need > (size_t)FSLBM_STATIC_WORKSPACE_BYTES) {
     g_init_error = "the lattice needs " + std::to_string(need) + " bytes of workspace, more than the " +
                    std::to_string((size_t)FSLBM_STATIC_WORKSPACE_BYTES) + " of the static workspace";
@@ -461,7 +486,7 @@ fslbm_status fslbm_init_static(const fslbm_params* p, const fslbm_buffers* b, fs
     ws = g_scratch_ptr[dev];
     g_scratch_busy[dev] = true;
   }
-  s = init_impl(p, b, ws, (size_t)FSLBM_STATIC_WORKSPACE_BYTES, false, out);
+  s = init_impl(p, b, ws, (size_t)FSLBM_STATIC_WORKSPACE_BYTES, false, false, out);
   std::lock_guard<std::mutex> lock(g_scratch_mu);
   if (s != FSLBM_OK) g_scratch_busy[dev] = false;
   else (*out)->static_device = dev;
@@ -481,7 +506,7 @@ static void forget_extent(fslbm_ctx* c) {
 static InitArgs init_args(fslbm_ctx* c) {
   InitArgs a;
   a.c = c->com;
-  a.f = c->f[c->cur];
+  a.f = c->f[c->fcur];
   a.flags = c->flags;
   a.mass = c->mass;
   a.phi = c->phi[c->cur];
@@ -521,7 +546,7 @@ fslbm_status health(fslbm_ctx* c, double sc[2], int32_t cn[8], int32_t last[NCOU
   HIPCHK(c, launch_fill_i32(c->cnt, 8, 0, c->stream), "stats init");
   StatArgs a;
   a.c = c->com;
-  a.f = c->f[c->cur];
+  a.f = c->f[c->fcur];
   a.flags = c->flags;
   a.mass = c->mass;
   a.acc = c->acc;
@@ -582,7 +607,7 @@ hipError_t sweep_box(fslbm_ctx* c, SweepArgs& s) {
   int by0 = 0, bny = g.ny, bz0 = 0, bnz = g.nz;
   bool empty = false;
   if (c->ext_valid >= 0) {
-    const int32_t* ex = c->ext_host + 4 * c->ext_valid;
+    const int32_t* ex = c->ext_host + EXT_VALUES * c->ext_valid;
     const int d = c->step - c->ext_step[c->ext_valid];
     if (ex[1] < 0) {
       empty = true;  // no fluid cell
@@ -599,7 +624,7 @@ hipError_t sweep_box(fslbm_ctx* c, SweepArgs& s) {
     hipError_t e = empty ? launch_extent(c->flags, g, 0, 1, 0, 1, c->ext_dev, (void*)c->stream)
                          : launch_extent(c->flags, g, by0, bny, bz0, bnz, c->ext_dev, (void*)c->stream);
     if (e == hipSuccess)
-      e = hipMemcpyAsync(c->ext_host + 4 * slot, c->ext_dev, 4 * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream);
+      e = hipMemcpyAsync(c->ext_host + EXT_VALUES * slot, c->ext_dev, EXT_VALUES * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipEventRecord(c->ext_ev[slot], c->stream);
     if (e != hipSuccess) return e;
     c->ext_step[slot] = c->step;
@@ -625,8 +650,8 @@ void step_args(const fslbm_ctx* c, StepLaunch& L) {
   const int a = c->cur, b = 1 - c->cur;
   SweepArgs& s = L.sweep;
   s.c = c->com;
-  s.fin = c->f[a];
-  s.fout = c->f[b];
+  s.fin = c->f[c->fcur];
+  s.fout = c->f[(c->fcur + 1) % c->nf];
   s.flags = c->flags;
   s.mass_in = c->mass;
   s.mass = c->mass;
@@ -659,7 +684,7 @@ void step_args(const fslbm_ctx* c, StepLaunch& L) {
   s.surf_d = c->surf_d;
   ConvArgs& v = L.conv;
   v.c = c->com;
-  v.fout = c->f[b];
+  v.fout = s.fout;
   v.flags = c->flags;
   v.mass = c->mass;
   v.phi_out = c->phi[b];
@@ -701,8 +726,9 @@ hipError_t resident_steps(fslbm_ctx* c, int m, int32_t rule) {
     SweepArgs& s = r.sweep[k] = L.sweep;
     ConvArgs& v = r.conv[k] = L.conv;
     const int in = k ? 1 - c->cur : c->cur;
-    s.fin = c->f[in];
-    s.fout = v.fout = c->f[1 - in];
+    const int fi = k ? 1 - c->fcur : c->fcur;  // two population buffers on lattices of this size
+    s.fin = c->f[fi];
+    s.fout = v.fout = c->f[1 - fi];
     s.phi_in = c->phi[in];
     s.phi_out = v.phi_out = c->phi[1 - in];
     s.counters = v.counters = c->counters + ((c->step + k) & 1) * NCOUNT;
@@ -722,6 +748,74 @@ hipError_t resident_steps(fslbm_ctx* c, int m, int32_t rule) {
   const hipError_t e = launch_resident(r, c->p.precision, rule, (void*)c->stream);
   if (e == hipSuccess) c->bar_flip = 1 - c->bar_flip;
   return e;
+}
+
+// Rows y < yd that the two-step kernel may take for the next two steps (0:
+// none): the run of rows at the lattice's low y end whose cells, and those of
+// the two rows above it, are liquid now.  From the latest extent that has
+// arrived: the cells that are not liquid reach at most one row further down per
+// step (a liquid cell converts next to an emptied interface cell).  The second
+// row is for a solid cell: the row next to it takes the wall closure.
+int pair_rows(const fslbm_ctx* c) {
+  if (!c->deep || c->timing || c->ext_every <= 0 || c->ext_valid < 0) return 0;
+  const Grid& g = c->com.grid;
+  const int32_t* ex = c->ext_host + EXT_VALUES * c->ext_valid;
+  const int d = c->step - c->ext_step[c->ext_valid];
+  // every row of the low end has fluid up to the z faces
+  if (ex[1] < 0 || ex[0] > 0 || (!g.pz && (ex[2] > 0 || ex[3] < g.nz - 1))) return 0;
+  const int yd = std::min(ex[4], g.ny) - d - 2;
+  return yd >= DEEP_ROWS ? yd : 0;
+}
+
+// One step; ylow > 0: its sweep leaves the rows y < ylow (to the two-step kernel).
+fslbm_status step_once(fslbm_ctx* c, int32_t rule, int ylow) {
+  StepLaunch L{};
+  step_args(c, L);
+  SweepArgs& s = L.sweep;
+  // the plain step with the four-lane interface kernel runs it before the
+  // sweep (the other variants after it)
+  const bool order = c->reorder && c->quad && !extra_step(s.c);
+  s.order = L.conv.order = order ? 1 : 0;
+  HIPCHK(c, sweep_box(c, s), "extent");
+  if (ylow > 0) {  // (with a row box that starts below: see pair_rows)
+    s.bny -= ylow - s.by0;
+    s.by0 = ylow;
+    s.shell = 1;
+  }
+  if (order) {
+    // the interface list of the current classes, when no step has left it
+    if (!c->list_ok)
+      HIPCHK(c, launch_list_append(c->flags, c->com.grid, s.counters + C_I, c->listI, c->islot, c->stream),
+             "interface list");
+    HIPCHK(c, launch_iface(L, c->p.precision, rule), "interface launch");
+  }
+  if (c->timing) {
+    while (c->events.size() < c->events_used + 2) {
+      hipEvent_t ev;
+      HIPCHK(c, hipEventCreate(&ev), "event create");
+      c->events.push_back(ev);
+    }
+    HIPCHK(c, hipEventRecord(c->events[c->events_used], c->stream), "event record");
+  }
+  HIPCHK(c, launch_sweep(L, c->p.precision, rule), "sweep launch");
+  if (c->timing) {
+    HIPCHK(c, hipEventRecord(c->events[c->events_used + 1], c->stream), "event record");
+    c->events_used += 2;
+  }
+  if (!order) {
+    if (s.nwall > 0) HIPCHK(c, launch_wall(L, c->p.precision), "wall launch");
+    if (c->kappa) HIPCHK(c, launch_curvature(L), "curvature launch");
+    HIPCHK(c, launch_iface(L, c->p.precision, rule), "interface launch");
+  }
+  if (!s.freeze) {
+    HIPCHK(c, launch_convert(L, c->p.precision), "conversion launch");
+    c->bar_flip = 1 - c->bar_flip;
+  }
+  c->list_ok = order;
+  c->cur = 1 - c->cur;
+  c->fcur = (c->fcur + 1) % c->nf;
+  c->step += 1;
+  return FSLBM_OK;
 }
 
 }  // namespace
@@ -749,52 +843,35 @@ fslbm_status fslbm_step(fslbm_ctx* c, int32_t n, int32_t rule) {
       if (c->check_every > 0) m = std::min<int32_t>(m, c->check_every - c->step % c->check_every);
       HIPCHK(c, resident_steps(c, m, rule), "resident launch");
       c->list_ok = false;
-      if (m & 1) c->cur = 1 - c->cur;
+      if (m & 1) {
+        c->cur = 1 - c->cur;
+        c->fcur = 1 - c->fcur;
+      }
       c->step += m;
       const fslbm_status hs = check_due(c);
       if (hs != FSLBM_OK) return hs;
       continue;
     }
-    StepLaunch L{};
-    step_args(c, L);
-    SweepArgs& s = L.sweep;
-    // the plain step with the four-lane interface kernel runs it before the
-    // sweep (the other variants after it)
-    const bool order = c->reorder && c->quad && !extra_step(s.c);
-    s.order = L.conv.order = order ? 1 : 0;
-    HIPCHK(c, sweep_box(c, s), "extent");
-    if (order) {
-      // the interface list of the current classes, when no step has left it
-      if (!c->list_ok)
-        HIPCHK(c, launch_list_append(c->flags, c->com.grid, s.counters + C_I, c->listI, c->islot, c->stream),
-               "interface list");
-      HIPCHK(c, launch_iface(L, c->p.precision, rule), "interface launch");
+    m = 1;
+    const int yd = pair_rows(c);
+    if (yd > 0 && n - i >= 2 && (c->check_every <= 0 || (c->step + 1) % c->check_every != 0)) {
+      // two steps: the rows below yd at once, into the buffer of the second;
+      // the others one after the other (the first with the row below them,
+      // which the second pulls from)
+      m = 2;
+      DeepArgs a{};
+      a.c = c->com;
+      a.fin = c->f[c->fcur];
+      a.fout = c->f[(c->fcur + 2) % 3];
+      a.yd = yd;
+      HIPCHK(c, launch_deep(a, c->p.precision, (void*)c->stream), "two-step launch");
+      fslbm_status st = step_once(c, rule, yd - 1);
+      if (st == FSLBM_OK) st = step_once(c, rule, yd);
+      if (st != FSLBM_OK) return st;
+    } else {
+      const fslbm_status st = step_once(c, rule, 0);
+      if (st != FSLBM_OK) return st;
     }
-    if (c->timing) {
-      while (c->events.size() < c->events_used + 2) {
-        hipEvent_t ev;
-        HIPCHK(c, hipEventCreate(&ev), "event create");
-        c->events.push_back(ev);
-      }
-      HIPCHK(c, hipEventRecord(c->events[c->events_used], c->stream), "event record");
-    }
-    HIPCHK(c, launch_sweep(L, c->p.precision, rule), "sweep launch");
-    if (c->timing) {
-      HIPCHK(c, hipEventRecord(c->events[c->events_used + 1], c->stream), "event record");
-      c->events_used += 2;
-    }
-    if (!order) {
-      if (s.nwall > 0) HIPCHK(c, launch_wall(L, c->p.precision), "wall launch");
-      if (c->kappa) HIPCHK(c, launch_curvature(L), "curvature launch");
-      HIPCHK(c, launch_iface(L, c->p.precision, rule), "interface launch");
-    }
-    if (!s.freeze) {
-      HIPCHK(c, launch_convert(L, c->p.precision), "conversion launch");
-      c->bar_flip = 1 - c->bar_flip;
-    }
-    c->list_ok = order;
-    c->cur = 1 - c->cur;
-    c->step += 1;
     const fslbm_status hs = check_due(c);
     if (hs != FSLBM_OK) return hs;
   }
@@ -810,7 +887,7 @@ fslbm_status fslbm_fields(fslbm_ctx* c, uint32_t mask, void* const* dst) {
   if (mask >> 8) { c->last_error = "unknown field bit"; return FSLBM_E_INVALID; }
   FieldArgs a;
   a.c = c->com;
-  a.f = c->f[c->cur];
+  a.f = c->f[c->fcur];
   a.flags = c->flags;
   a.mass = c->mass;
   a.phi = c->phi[c->cur];
@@ -1340,7 +1417,7 @@ fslbm_status fslbm_window_forward(fslbm_ctx* c, int32_t T, int32_t K, int32_t ru
   // checkpoint 0: the current state of the context
   const size_t fb = Q * N * storage_bytes(c->p.precision);
   const fslbm_window::State& c0 = w->ckpt[0];
-  if ((e = hipMemcpyAsync(c0.f, c->f[c->cur], fb, hipMemcpyDeviceToDevice, c->stream)) != hipSuccess ||
+  if ((e = hipMemcpyAsync(c0.f, c->f[c->fcur], fb, hipMemcpyDeviceToDevice, c->stream)) != hipSuccess ||
       (e = hipMemcpyAsync(c0.m, c->mass, 8 * N, hipMemcpyDeviceToDevice, c->stream)) != hipSuccess ||
       (e = hipMemcpyAsync(c0.phi, c->phi[c->cur], 8 * N, hipMemcpyDeviceToDevice, c->stream)) != hipSuccess)
     return fail(dev_fail(c, e, "checkpoint copy"));
@@ -1355,7 +1432,7 @@ fslbm_status fslbm_window_forward(fslbm_ctx* c, int32_t T, int32_t K, int32_t ru
   w->rec_seg = w->C - 1;
   // the final state becomes the context's current state
   const fslbm_window::State& fin = state_at(w, T);
-  if ((e = hipMemcpyAsync(c->f[c->cur], fin.f, fb, hipMemcpyDeviceToDevice, c->stream)) != hipSuccess ||
+  if ((e = hipMemcpyAsync(c->f[c->fcur], fin.f, fb, hipMemcpyDeviceToDevice, c->stream)) != hipSuccess ||
       (e = hipMemcpyAsync(c->mass, fin.m, 8 * N, hipMemcpyDeviceToDevice, c->stream)) != hipSuccess ||
       (e = hipMemcpyAsync(c->phi[c->cur], fin.phi, 8 * N, hipMemcpyDeviceToDevice, c->stream)) != hipSuccess)
     return fail(dev_fail(c, e, "final state copy"));

@@ -64,6 +64,7 @@ struct SweepArgs {
   // box of rows the sweep launches (box != 0): y in [by0, by0 + bny), z in
   // [bz0, bz0 + bnz); every liquid cell lies inside it.  0: every row.
   int box, by0, bny, bz0, bnz;
+  int shell; // the box leaves the rows below to the two-step kernel
   int pairs; // FP16 form: two cells per lane when rows have even length
   int quad;  // interface cells of the plain step with four lanes per cell (k_iface4); 2: XCD-aware order
   // order != 0: the interface kernel runs before the sweep.  It takes the
@@ -167,6 +168,26 @@ constexpr int RESIDENT_STEPS = 256;
 // conversions: 32.4 us with 8, 35.3 with 64.
 constexpr int SOLO_CELLS = 8;
 
+// Two steps of the rows y < yd (every cell of the rows y <= yd is liquid).
+struct DeepArgs {
+  Common c;
+  const void* fin;
+  void* fout;
+  int yd;
+  int ntx, nty, nzc, zlen, per;  // tiles, set by the launcher
+};
+// Where the two-step kernel runs: the FP64 and FP32 forms, lattices whose
+// population buffers have left the 256 MB cache (us a step of a tank, one step
+// after the other / two at once: 128x96x128 FP64 85 / 85, FP32 47 / 57;
+// 160x120x160 FP64 136 / 128, FP32 80 / 84; 192x128x192 FP64 212 / 173, FP32
+// 111 / 104; 256x160x256 FP64 460 / 371, FP32 239 / 185; 512x320x512 FP64 2917
+// / 2289, FP32 1564 / 1170), up to 17 GB a buffer (a third one of it is needed),
+// and from two tiles of rows on.  FP16 storage is bound by its arithmetic there:
+// 512x320x512 848 / 832, 256x160x256 144 / 159.
+constexpr double DEEP_MIN_BYTES = 300e6;
+constexpr double DEEP_MAX_BYTES = 17e9;
+constexpr int DEEP_ROWS = 24;
+
 struct InitArgs {
   Common c;
   void* f;
@@ -239,7 +260,9 @@ struct AdjArgs {
 };
 
 hipError_t launch_sweep(const StepLaunch& L, int precision, int rule);
-// y and z extent of the fluid cells into ext = (ymin, ymax, zmin, zmax); (INT_MAX, -1, ...) if none
+// y and z extent of the fluid cells, and the lowest y of a cell that is not
+// liquid, into ext = (ymin, ymax, zmin, zmax, ynot); (INT_MAX, -1, ..., INT_MAX) if none
+constexpr int EXT_VALUES = 5;
 // partial extents of k_extent (ext holds (1 + EXT_COPIES) lines of 32 int32:
 // the result in the first, the partials after it)
 constexpr int EXT_COPIES = 64;
@@ -259,6 +282,7 @@ hipError_t launch_list_append(const uint8_t* flags, const Grid& g, int32_t* coun
 hipError_t launch_fill_i32(int32_t* p, size_t n, int32_t v, void* stream);
 hipError_t launch_fill_f64(double* p, size_t n, double v, void* stream);
 hipError_t launch_check_flags(const uint8_t* flags, const Grid& g, int32_t* err, void* stream);
+hipError_t launch_deep(const DeepArgs& a, int precision, void* stream);
 hipError_t launch_wall(const StepLaunch& L, int precision);
 hipError_t launch_check_walls(const uint8_t* flags, const Grid& g, const int32_t* cells, int n, const double* delta,
                               const double* uw, int32_t* err, int32_t* count, void* stream);

@@ -57,10 +57,15 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(SweepArgs a) {
   const unsigned rbase = (unsigned)row * (unsigned)g.nx;
   const uint8_t t = x < g.nx ? a.flags[rbase + x] : GAS;
   const int lane = (int)threadIdx.x & 63;
+  // interface cells -> list; with the interface kernel first that of the next
+  // step, here only where the launch is the rows at the surface alone (else one
+  // atomic per wavefront after the collision is faster: 128 tank 27.2 against
+  // 28.4 us)
   const unsigned long long b = __ballot(t == IFACE);
-  if constexpr (!ORDER1) {
-    // interface cells -> list
-    const int pos = block_reserve<BLOCK / 64>(__popcll(b), &a.counters[C_I]) + __popcll(b & ((1ull << lane) - 1ull));
+  int pos = -1;
+  if (!ORDER1 || a.shell) {
+    pos = block_reserve<BLOCK / 64>(__popcll(b), (ORDER1 ? a.counters_next : a.counters) + C_I) +
+          __popcll(b & ((1ull << lane) - 1ull));
     if (t == IFACE) a.listI[pos] = (int)(rbase + x);
   }
   // with the interface kernel first, a wavefront without liquid cells that
@@ -135,7 +140,7 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(SweepArgs a) {
     // With the interface kernel first (a wavefront with interface cells has
     // come this far, and every lane of the row but none past its end): the
     // list entry of time t of an interface cell, then its entry in the next
-    // list.  The map is read at interface cells only; a wavefront with
+    // list (pos).  The map is read at interface cells only; a wavefront with
     // interface cells writes its whole segment of it (-1 elsewhere), so no
     // line of it is left partly written.  An interface cell stores what the
     // interface kernel computed for it (a list entry beyond rcap: written
@@ -143,8 +148,8 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(SweepArgs a) {
     const bool it = t == IFACE;
     int oslot = -1;
     if (it) oslot = a.islot[rbase + x];
-    const int pos = wave_append_at(it, &a.counters_next[C_I], a.listI, (int)(rbase + x));
-    if (b != 0ull) a.islot[rbase + x] = pos;
+    if (!a.shell) pos = wave_append_at(it, &a.counters_next[C_I], a.listI, (int)(rbase + x));
+    if (b != 0ull) a.islot[rbase + x] = it ? pos : -1;
     const bool keep = it && (unsigned)oslot >= (unsigned)a.rcap;
     if (it && !keep) {
       const S* __restrict__ rb = reinterpret_cast<const S*>(a.rbuf) + oslot;
@@ -326,13 +331,13 @@ __global__ __launch_bounds__(BLOCK) void k_sweep_h2(SweepArgs a) {
   }
 }
 
-// Extent of the fluid (liquid and interface) cells in y and z: ext[0..3] =
-// (ymin, ymax, zmin, zmax).  Only the rows of the box [y0, y0 + ny) x
+// Extent of the fluid (liquid and interface) cells in y and z, and the lowest
+// row with a cell that is not liquid: ext[0..4] = (ymin, ymax, zmin, zmax, ynot).  Only the rows of the box [y0, y0 + ny) x
 // [z0, z0 + nz) are read (the caller knows the fluid lies inside it).  A lane
 // reads 16 flag bytes of a row (one 16-byte load where the row allows); each
 // block adds its extent to one of EXT_COPIES partial extents (one atomic per
 // value; spread over copies so that the blocks do not queue on one address),
-// and k_extent_final reduces the copies into ext[0..3] and resets them for the
+// and k_extent_final reduces the copies into ext[0..4] and resets them for the
 // next measurement (k_extent_init sets them once, when the context is made).
 constexpr int EBLOCK = 256;
 constexpr int ECELLS = 16;
@@ -343,6 +348,7 @@ __device__ __forceinline__ void extent_reset(int32_t* e) {
   e[1] = -1;
   e[2] = 0x7fffffff;
   e[3] = -1;
+  e[4] = 0x7fffffff;
 }
 
 __global__ void k_extent_init(int32_t* ext) {
@@ -351,17 +357,17 @@ __global__ void k_extent_init(int32_t* ext) {
 
 __global__ __launch_bounds__(EBLOCK) void k_extent(const uint8_t* __restrict__ flags, Grid g, int y0, int ny, int z0,
                                                    int nz, int32_t* ext) {
-  __shared__ int sm[4][EBLOCK / 64];
+  __shared__ int sm[EXT_VALUES][EBLOCK / 64];
   const int lpr = (g.nx + ECELLS - 1) / ECELLS;
   const int total = ny * nz * lpr;  // < N / 16 + ny nz < 2^31
-  int ymin = 0x7fffffff, ymax = -1, zmin = 0x7fffffff, zmax = -1;
+  int ymin = 0x7fffffff, ymax = -1, zmin = 0x7fffffff, zmax = -1, ynot = 0x7fffffff;
   for (int k = (int)blockIdx.x * EBLOCK + (int)threadIdx.x; k < total; k += (int)gridDim.x * EBLOCK) {
     const int brow = k / lpr;
     const int x0 = (k - brow * lpr) * ECELLS;
     const int by = brow % ny;
     const int y = y0 + by, z = z0 + (brow - by) / ny;
     const size_t o = ((size_t)z * g.ny + (size_t)y) * (size_t)g.nx + (size_t)x0;
-    bool fluid = false;
+    bool fluid = false, other = false;
     if (x0 + ECELLS <= g.nx && (o & 15u) == 0u) {
       const uint4 v = *reinterpret_cast<const uint4*>(flags + o);
       const uint32_t w[4] = {v.x, v.y, v.z, v.w};
@@ -369,10 +375,16 @@ __global__ __launch_bounds__(EBLOCK) void k_extent(const uint8_t* __restrict__ f
       for (int j = 0; j < ECELLS; ++j) {
         const uint32_t b = (w[j >> 2] >> (8 * (j & 3))) & 0xffu;
         fluid = fluid || b == IFACE || b == LIQ;
+        other = other || b != LIQ;
       }
     } else {
-      for (int j = 0; j < ECELLS && x0 + j < g.nx; ++j) fluid = fluid || flags[o + j] == IFACE || flags[o + j] == LIQ;
+      for (int j = 0; j < ECELLS && x0 + j < g.nx; ++j) {
+        const uint8_t b = flags[o + j];
+        fluid = fluid || b == IFACE || b == LIQ;
+        other = other || b != LIQ;
+      }
     }
+    if (other) ynot = min(ynot, y);
     if (fluid) {
       ymin = min(ymin, y);
       ymax = max(ymax, y);
@@ -385,12 +397,14 @@ __global__ __launch_bounds__(EBLOCK) void k_extent(const uint8_t* __restrict__ f
     ymax = max(ymax, __shfl_down(ymax, off));
     zmin = min(zmin, __shfl_down(zmin, off));
     zmax = max(zmax, __shfl_down(zmax, off));
+    ynot = min(ynot, __shfl_down(ynot, off));
   }
   if ((threadIdx.x & 63) == 0) {
     sm[0][threadIdx.x >> 6] = ymin;
     sm[1][threadIdx.x >> 6] = ymax;
     sm[2][threadIdx.x >> 6] = zmin;
     sm[3][threadIdx.x >> 6] = zmax;
+    sm[4][threadIdx.x >> 6] = ynot;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -399,9 +413,11 @@ __global__ __launch_bounds__(EBLOCK) void k_extent(const uint8_t* __restrict__ f
       ymax = max(ymax, sm[1][w]);
       zmin = min(zmin, sm[2][w]);
       zmax = max(zmax, sm[3][w]);
+      ynot = min(ynot, sm[4][w]);
     }
+    int32_t* e = ext + ESTRIDE * (1 + (int)(blockIdx.x % EXT_COPIES));
+    if (ynot < 0x7fffffff) atomicMin(&e[4], ynot);
     if (ymax >= 0) {
-      int32_t* e = ext + ESTRIDE * (1 + (int)(blockIdx.x % EXT_COPIES));
       atomicMin(&e[0], ymin);
       atomicMax(&e[1], ymax);
       atomicMin(&e[2], zmin);
@@ -412,19 +428,20 @@ __global__ __launch_bounds__(EBLOCK) void k_extent(const uint8_t* __restrict__ f
 
 __global__ void k_extent_final(int32_t* ext) {
   const int c = (int)threadIdx.x;  // EXT_COPIES threads: one wavefront
-  int v[4];
+  int v[EXT_VALUES];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = ext[ESTRIDE * (1 + c) + i];
+  for (int i = 0; i < EXT_VALUES; ++i) v[i] = ext[ESTRIDE * (1 + c) + i];
   extent_reset(ext + ESTRIDE * (1 + c));
   for (int off = 32; off > 0; off >>= 1) {
     v[0] = min(v[0], __shfl_down(v[0], off));
     v[1] = max(v[1], __shfl_down(v[1], off));
     v[2] = min(v[2], __shfl_down(v[2], off));
     v[3] = max(v[3], __shfl_down(v[3], off));
+    v[4] = min(v[4], __shfl_down(v[4], off));
   }
   if (c == 0)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) ext[i] = v[i];
+    for (int i = 0; i < EXT_VALUES; ++i) ext[i] = v[i];
 }
 
 hipError_t launch_extent_init(int32_t* ext, void* stream) {
