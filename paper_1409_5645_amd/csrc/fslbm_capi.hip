@@ -803,7 +803,6 @@ fslbm_status step_once(fslbm_ctx* c, int32_t rule, int ylow) {
     c->events_used += 2;
   }
   if (!order) {
-    if (s.nwall > 0) HIPCHK(c, launch_wall(L, c->p.precision), "wall launch");
     if (c->kappa) HIPCHK(c, launch_curvature(L), "curvature launch");
     HIPCHK(c, launch_iface(L, c->p.precision, rule), "interface launch");
   }

@@ -105,6 +105,7 @@ struct SweepArgs {
   const double* wdelta;
   const double* wuw;
   int nwall;
+  int nbw;   // blocks of the interface kernel for the wall list (set by the launcher)
 };
 
 struct ConvArgs {
@@ -283,7 +284,6 @@ hipError_t launch_fill_i32(int32_t* p, size_t n, int32_t v, void* stream);
 hipError_t launch_fill_f64(double* p, size_t n, double v, void* stream);
 hipError_t launch_check_flags(const uint8_t* flags, const Grid& g, int32_t* err, void* stream);
 hipError_t launch_deep(const DeepArgs& a, int precision, void* stream);
-hipError_t launch_wall(const StepLaunch& L, int precision);
 hipError_t launch_check_walls(const uint8_t* flags, const Grid& g, const int32_t* cells, int n, const double* delta,
                               const double* uw, int32_t* err, int32_t* count, void* stream);
 hipError_t launch_set_equilibrium(const InitArgs& a, int precision, const double* rho, const double* u,
