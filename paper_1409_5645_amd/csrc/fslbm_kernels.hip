@@ -245,15 +245,18 @@ __device__ __forceinline__ double iface_compute(IfaceData<F>& d, const Common& c
 // registers, store.
 constexpr int IBLOCK = 64;  // interface-list kernels: one wavefront per block
 
-// EXTRA: moving walls, surface tension or the PLIC interface position present
-// (a separate instantiation, so that the plain path keeps its registers).
+// EXTRA = 1: moving walls, surface tension or the PLIC interface position
+// present; 2: solid cells present, with or without those (instantiations of
+// their own: the plain path keeps its registers, and with the solid cells' code
+// the FP32 forms of EXTRA = 1 would spill a hundred).
 // Waves per SIMD the FP32-arithmetic forms are compiled for (the FP64 form
 // takes what it needs): 4 (128 VGPRs) for the plain FSK and FSL rules, 3 (168)
-// for the rules with a boundary shear and the EXTRA variants, 2 for the EXTRA
-// variant of FSL with a prescribed shear; each without spills.
-template <class F, int RULE, bool EXTRA>
+// for the rules with a boundary shear and EXTRA = 1, 2 for EXTRA = 2 and for
+// EXTRA = 1 of FSL with a prescribed shear; each without spills.
+template <class F, int RULE, int EXTRA>
 constexpr int iface_waves() {
   if (sizeof(typename F::R) != 4) return 1;
+  if (EXTRA == 2) return 2;
   if (EXTRA) return RULE == 5 ? 2 : 3;
   return (RULE & 6) ? 3 : 4;
 }
@@ -322,7 +325,7 @@ __device__ __forceinline__ void wall_cells(const SweepArgs& a, int tid, int nth)
   }
 }
 
-template <class F, int RULE, bool REC = false, bool EXTRA = false>
+template <class F, int RULE, bool REC = false, int EXTRA = 0>
 __global__ __launch_bounds__(IBLOCK, (iface_waves<F, RULE, EXTRA>())) void k_iface(SweepArgs a) {
   using R = typename F::R;
   using S = typename F::S;
@@ -335,11 +338,13 @@ __global__ __launch_bounds__(IBLOCK, (iface_waves<F, RULE, EXTRA>())) void k_ifa
   const float isc = a.c.inv_scale;
   // The first nbw blocks take the liquid cells next to solid cells: both kinds
   // of cell are few and wait on memory, so they run beside one another (192 x 96
-  // x 64 tank on a ramp, FP64: two kernels 16.0 + 15.9 us, this one 17.8).
-  const int nbw = EXTRA ? a.nbw : 0;
-  if (EXTRA && (int)blockIdx.x < nbw) {
-    wall_cells<F>(a, (int)(blockIdx.x * IBLOCK + threadIdx.x), nbw * IBLOCK);
-    return;
+  // x 64 tank on a ramp, FP64: two kernels 16.0 + 15.9 us, this one 17.1).
+  const int nbw = EXTRA == 2 ? a.nbw : 0;
+  if constexpr (EXTRA == 2) {
+    if ((int)blockIdx.x < nbw) {
+      wall_cells<F>(a, (int)(blockIdx.x * IBLOCK + threadIdx.x), nbw * IBLOCK);
+      return;
+    }
   }
   const int nth = ((int)gridDim.x - nbw) * IBLOCK;
   for (int i = ((int)blockIdx.x - nbw) * IBLOCK + (int)threadIdx.x; i < n_i; i += nth) {
@@ -384,23 +389,21 @@ __global__ __launch_bounds__(IBLOCK, (iface_waves<F, RULE, EXTRA>())) void k_ifa
     }
     d.m = a.mass_in[idx];
     d.phix = a.phi_in[idx];
-    if constexpr (EXTRA) {
-      if (a.c.solid) {
-        // solid pull sources (class SOLID, inside the grid): the cell's own fill
-        // for the geometry, the wall closure for the populations
-        uint32_t sm = 0, up = 0;
+    if constexpr (EXTRA == 2) {
+      // solid pull sources (class SOLID, inside the grid): the cell's own fill
+      // for the geometry, the wall closure for the populations
+      uint32_t sm = 0, up = 0;
 #define FSLBM_ISOLID(q)                                                       \
   if (d.ty[q] == WALL_CLASS && pull_source<q>(g, n) >= 0) sm |= 1u << q;      \
   if (d.ty[q] == LIQ || d.ty[q] == IFACE) up |= 1u << q;
-        FSLBM_LINKS(FSLBM_ISOLID)
+      FSLBM_LINKS(FSLBM_ISOLID)
 #undef FSLBM_ISOLID
-        if (sm) {
-          const int slot = wall_slot(a.wcells, a.nwall, idx);
-          if (slot >= 0) solid_links<R>(d.f, d.own, sm, up, slot, a.nwall, a.wdelta, a.wuw);
+      if (sm) {
+        const int slot = wall_slot(a.wcells, a.nwall, idx);
+        if (slot >= 0) solid_links<R>(d.f, d.own, sm, up, slot, a.nwall, a.wdelta, a.wuw);
 #pragma unroll
-          for (int q = 1; q < Q; ++q)
-            if ((sm >> q) & 1u) d.ph[q] = d.phix;
-        }
+        for (int q = 1; q < Q; ++q)
+          if ((sm >> q) & 1u) d.ph[q] = d.phix;
       }
     }
     if constexpr (REC) {
@@ -421,7 +424,7 @@ __global__ __launch_bounds__(IBLOCK, (iface_waves<F, RULE, EXTRA>())) void k_ifa
     // ---- phase 2: interface treatment and collision
     R rho_s, u[3];
     const double drho = (EXTRA && a.c.sigma != 0.0) ? a.kappa[i] : 0.0;
-    const double m_new = iface_compute<F, RULE, EXTRA>(d, a.c, rho_s, u, n, fin, drho, a.flags, a.phi_in, a.surf_n,
+    const double m_new = iface_compute<F, RULE, EXTRA != 0>(d, a.c, rho_s, u, n, fin, drho, a.flags, a.phi_in, a.surf_n,
                                                        a.surf_d);
     // ---- phase 3: populations, fill level and classification (FP64 bookkeeping)
 #pragma unroll
@@ -855,11 +858,18 @@ __global__ __launch_bounds__(BLOCK) void k_stats(StatArgs a) {
 static inline unsigned blocks_for(size_t n) { return (unsigned)((n + BLOCK - 1) / BLOCK); }
 static constexpr unsigned IFACE_GRID = 8192;
 
-template <class F, int RULE, bool REC, bool EXTRA>
+template <class F, int RULE, bool REC, int EXTRA>
 static void iface_go(const StepLaunch& L, unsigned nb) {
   SweepArgs a = L.sweep;
-  a.nbw = EXTRA && a.nwall > 0 ? (int)std::min<unsigned>(IFACE_GRID, (unsigned)((a.nwall + IBLOCK - 1) / IBLOCK)) : 0;
+  a.nbw = EXTRA == 2 && a.nwall > 0 ? (int)std::min<unsigned>(IFACE_GRID, (unsigned)((a.nwall + IBLOCK - 1) / IBLOCK)) : 0;
   k_iface<F, RULE, REC, EXTRA><<<nb + (unsigned)a.nbw, IBLOCK, 0, (hipStream_t)L.stream>>>(a);
+}
+
+template <class F, int RULE>
+static void iface_rule(const StepLaunch& L, unsigned nb, bool extra) {
+  if (L.sweep.c.solid) iface_go<F, RULE, false, 2>(L, nb);
+  else if (extra) iface_go<F, RULE, false, 1>(L, nb);
+  else iface_go<F, RULE, false, 0>(L, nb);
 }
 
 template <class F>
@@ -879,9 +889,9 @@ static void iface_form(const StepLaunch& L, int rule) {
     }
     const unsigned nbr = std::min<unsigned>(nb, (unsigned)((L.sweep.rec_cap + IBLOCK - 1) / IBLOCK));
     if (rule == 0)
-      extra ? iface_go<F, 0, true, true>(L, nbr) : iface_go<F, 0, true, false>(L, nbr);
+      extra ? iface_go<F, 0, true, 1>(L, nbr) : iface_go<F, 0, true, 0>(L, nbr);
     else
-      extra ? iface_go<F, 1, true, true>(L, nbr) : iface_go<F, 1, true, false>(L, nbr);
+      extra ? iface_go<F, 1, true, 1>(L, nbr) : iface_go<F, 1, true, 0>(L, nbr);
     return;
   }
   if (!extra && L.sweep.quad) {
@@ -889,12 +899,12 @@ static void iface_form(const StepLaunch& L, int rule) {
     return;
   }
   switch (rule) {
-    case 0: extra ? iface_go<F, 0, false, true>(L, nb) : iface_go<F, 0, false, false>(L, nb); break;
-    case 1: extra ? iface_go<F, 1, false, true>(L, nb) : iface_go<F, 1, false, false>(L, nb); break;
-    case 2: extra ? iface_go<F, 2, false, true>(L, nb) : iface_go<F, 2, false, false>(L, nb); break;
-    case 3: extra ? iface_go<F, 3, false, true>(L, nb) : iface_go<F, 3, false, false>(L, nb); break;
-    case 4: extra ? iface_go<F, 4, false, true>(L, nb) : iface_go<F, 4, false, false>(L, nb); break;
-    default: extra ? iface_go<F, 5, false, true>(L, nb) : iface_go<F, 5, false, false>(L, nb); break;
+    case 0: iface_rule<F, 0>(L, nb, extra); break;
+    case 1: iface_rule<F, 1>(L, nb, extra); break;
+    case 2: iface_rule<F, 2>(L, nb, extra); break;
+    case 3: iface_rule<F, 3>(L, nb, extra); break;
+    case 4: iface_rule<F, 4>(L, nb, extra); break;
+    default: iface_rule<F, 5>(L, nb, extra); break;
   }
 }
 
