@@ -803,7 +803,7 @@ fslbm_status step_once(fslbm_ctx* c, int32_t rule, int ylow) {
     c->events_used += 2;
   }
   if (!order) {
-    if (c->kappa) HIPCHK(c, launch_curvature(L), "curvature launch");
+    HIPCHK(c, launch_geometry(L, rule), "geometry launch");
     HIPCHK(c, launch_iface(L, c->p.precision, rule), "interface launch");
   }
   if (!s.freeze) {

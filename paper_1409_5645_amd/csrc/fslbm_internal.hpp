@@ -273,7 +273,9 @@ hipError_t launch_extent(const uint8_t* flags, const Grid& g, int y0, int ny, in
                          void* stream);
 hipError_t launch_iface(const StepLaunch& L, int precision, int rule);
 hipError_t launch_iface4(const StepLaunch& L, int precision, int rule);  // fslbm_iface4.hip
-hipError_t launch_curvature(const StepLaunch& L);  // one or (plic = 2) two list kernels
+// geometry of the listed cells that needs more than the interface kernel loads:
+// curvature (sigma != 0), height functions (plic = 2); nothing without either
+hipError_t launch_geometry(const StepLaunch& L, int rule);
 hipError_t launch_convert(const StepLaunch& L, int precision);
 hipError_t launch_resident(const ResidentArgs& r, int precision, int rule, void* stream);
 // interface cells of the current classes -> list, islot, *counter (a step with

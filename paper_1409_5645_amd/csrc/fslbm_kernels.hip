@@ -22,6 +22,7 @@
 #include "fslbm_convert.hpp"
 #include "fslbm_device.hpp"
 #include "fslbm_internal.hpp"
+#include "fslbm_quad.hpp"
 #include "fslbm_stencil.hpp"
 
 #include <algorithm>
@@ -133,8 +134,7 @@ template <class F, int RULE, bool EXTRA>
 __device__ __forceinline__ double iface_compute(IfaceData<F>& d, const Common& cm, typename F::R& rho_s,
                                                 typename F::R (&u)[3], const Nbr& nb,
                                                 const typename F::S* __restrict__ fin, double drho,
-                                                const uint8_t* __restrict__ flags = nullptr,
-                                                const double* __restrict__ phi = nullptr,
+                                                const double* hfn = nullptr,
                                                 const double* __restrict__ surf_n = nullptr,
                                                 const double* __restrict__ surf_d = nullptr) {
   using R = typename F::R;
@@ -184,7 +184,12 @@ __device__ __forceinline__ double iface_compute(IfaceData<F>& d, const Common& c
     if constexpr (EXTRA && (RULE & 1) != 0) {
       // FSL link distances from the plane that cuts the cell's fill (PLIC),
       // with the height-function normal where its columns are complete
-      if (cm.plic == 2 && have_n) hf_normal(cm.grid, nb.x, nb.y, nb.z, flags, phi, nv);
+      // (both from k_columns, which leaves the normal in the cell's aux entry)
+      if (cm.plic == 2 && have_n) {
+        nv[0] = hfn[1];
+        nv[1] = hfn[2];
+        nv[2] = hfn[3];
+      }
       if (cm.plic && have_n) dist = plic_plane_offset(d.phix, nv);
     }
     if constexpr (EXTRA) {
@@ -217,7 +222,7 @@ __device__ __forceinline__ double iface_compute(IfaceData<F>& d, const Common& c
       for (int i = 0; i < 6; ++i) Sb[i] = (R)cm.shear_b[i];
     }
     // Laplace pressure: the boundary term takes P_b - sigma kappa (Eq.
-    // freeboundary); drho = 3 sigma kappa comes from k_curvature (0 without a normal)
+    // freeboundary); drho = 3 sigma kappa comes from k_curvature or k_columns (0 without a normal)
     R rhob_c = k.rhob_s, rho0b_c = k.rho0b;
     if constexpr (EXTRA) {
       if (cm.sigma != 0.0) {
@@ -325,6 +330,59 @@ __device__ __forceinline__ void wall_cells(const SweepArgs& a, int tid, int nth)
   }
 }
 
+// kappa of an interface cell from the fill seen over its D3Q19 neighbourhood
+__device__ __forceinline__ double fill_kappa(const SweepArgs& a, const Grid& g, int idx, const Nbr& n) {
+  IfaceData<FormF64> d;
+  d.phix = a.phi_in[idx];
+#define FSLBM_CLOAD(q)                                            \
+  {                                                               \
+    const int s = pull_source<q>(g, n);                           \
+    const int sc = s >= 0 ? s : idx;                              \
+    d.ty[q] = s >= 0 ? a.flags[sc] : WALL_CLASS;                  \
+    d.ph[q] = a.phi_in[sc];                                       \
+  }
+  FSLBM_LINKS(FSLBM_CLOAD)
+#undef FSLBM_CLOAD
+  if (a.c.solid) {
+    // a solid source is a wall: the cell's own fill
+#pragma unroll
+    for (int q = 1; q < Q; ++q)
+      if (d.ty[q] == WALL_CLASS) d.ph[q] = d.phix;
+  }
+  return curvature(d);
+}
+
+// kappa of an interface cell with plic = 2: its own height-function kappa;
+// where its columns are not complete, the mean of those of its D3Q19 interface
+// neighbours that have one (summed in link order: the neighbours lie on the
+// same stretch of surface, while the central-difference kappa of the raw fills
+// is biased by the fill itself); with no such neighbour the central-difference
+// kappa.  Every interface cell is listed, so khf holds this step's value at
+// every interface neighbour.
+__device__ __forceinline__ double hf_kappa(const SweepArgs& a, const Grid& g, int idx, const Nbr& n) {
+  const double kap = a.khf[idx];
+  if (!isnan(kap)) return kap;
+  double sum = 0.0, v[Q];
+  int cnt = 0;
+  uint8_t t[Q];
+#define FSLBM_HKLOAD(q)                                                  \
+  {                                                                      \
+    const int s = neighbor(g, n.x, n.y, n.z, CX[q], CY[q], CZ[q]);       \
+    const int sc = s >= 0 ? s : idx; /* NaN there: takes no part */      \
+    t[q] = a.flags[sc];                                                  \
+    v[q] = a.khf[sc];                                                    \
+  }
+  FSLBM_LINKS(FSLBM_HKLOAD)
+#undef FSLBM_HKLOAD
+#pragma unroll
+  for (int q = 1; q < Q; ++q)
+    if (t[q] == IFACE && !isnan(v[q])) {
+      sum = sum + v[q];
+      ++cnt;
+    }
+  return cnt ? sum / (double)cnt : fill_kappa(a, g, idx, n);
+}
+
 template <class F, int RULE, bool REC = false, int EXTRA = 0>
 __global__ __launch_bounds__(IBLOCK, (iface_waves<F, RULE, EXTRA>())) void k_iface(SweepArgs a) {
   using R = typename F::R;
@@ -357,6 +415,8 @@ __global__ __launch_bounds__(IBLOCK, (iface_waves<F, RULE, EXTRA>())) void k_ifa
     n.yp = step_axis(n.y, 1, g.ny, g.py);
     n.zm = step_axis(n.z, -1, g.nz, g.pz);
     n.zp = step_axis(n.z, 1, g.nz, g.pz);
+    double drho = 0.0;
+    if (EXTRA && a.c.sigma != 0.0) drho = a.c.plic == 2 ? 3.0 * a.c.sigma * hf_kappa(a, g, idx, n) : a.kappa[i];
     // ---- phase 1: loads.  Pull, Eq. (lbe1): f_q(x) = ft_q(x - c_q); beyond a
     // wall halfway bounce-back f_q(x) = ft_qbar(x).
     IfaceData<F> d;
@@ -423,8 +483,7 @@ __global__ __launch_bounds__(IBLOCK, (iface_waves<F, RULE, EXTRA>())) void k_ifa
     }
     // ---- phase 2: interface treatment and collision
     R rho_s, u[3];
-    const double drho = (EXTRA && a.c.sigma != 0.0) ? a.kappa[i] : 0.0;
-    const double m_new = iface_compute<F, RULE, EXTRA != 0>(d, a.c, rho_s, u, n, fin, drho, a.flags, a.phi_in, a.surf_n,
+    const double m_new = iface_compute<F, RULE, EXTRA != 0>(d, a.c, rho_s, u, n, fin, drho, a.aux + 4 * (size_t)idx, a.surf_n,
                                                        a.surf_d);
     // ---- phase 3: populations, fill level and classification (FP64 bookkeeping)
 #pragma unroll
@@ -449,11 +508,10 @@ __global__ __launch_bounds__(IBLOCK, (iface_waves<F, RULE, EXTRA>())) void k_ifa
   }
 }
 
-// Laplace-pressure correction of each listed interface cell (surface tension):
-// kappa[i] = 3 sigma kappa, with kappa = -div n from the fill seen over the
-// D3Q19 neighbourhood (Eq. freeboundary; see curvature), or with plic = 2 from
-// the height function where its columns are complete.  Runs between the
-// sweep (which builds the list) and k_iface, only when sigma != 0.
+// Laplace-pressure correction of each listed interface cell (surface tension
+// without height functions): kappa[i] = 3 sigma kappa, with kappa = -div n from
+// the fill seen over the D3Q19 neighbourhood (Eq. freeboundary; see curvature).
+// Runs between the sweep (which builds the list) and k_iface.
 __global__ __launch_bounds__(IBLOCK) void k_curvature(SweepArgs a) {
   const Grid g = a.c.grid;
   const int n_i = a.counters[C_I];
@@ -467,78 +525,69 @@ __global__ __launch_bounds__(IBLOCK) void k_curvature(SweepArgs a) {
     n.yp = step_axis(n.y, 1, g.ny, g.py);
     n.zm = step_axis(n.z, -1, g.nz, g.pz);
     n.zp = step_axis(n.z, 1, g.nz, g.pz);
-    IfaceData<FormF64> d;
-    d.phix = a.phi_in[idx];
-#define FSLBM_CLOAD(q)                                            \
-  {                                                               \
-    const int s = pull_source<q>(g, n);                           \
-    const int sc = s >= 0 ? s : idx;                              \
-    d.ty[q] = s >= 0 ? a.flags[sc] : WALL_CLASS;                  \
-    d.ph[q] = a.phi_in[sc];                                       \
-  }
-    FSLBM_LINKS(FSLBM_CLOAD)
-#undef FSLBM_CLOAD
-    if (a.c.solid) {
-      // a solid source is a wall: the cell's own fill
-#pragma unroll
-      for (int q = 1; q < Q; ++q)
-        if (d.ty[q] == WALL_CLASS) d.ph[q] = d.phix;
-    }
-    const double kap = curvature(d);
-    if (a.c.plic == 2) {
-      // height-function kappa where the columns along the axis of the
-      // central-difference normal are complete (NaN otherwise) for
-      // k_curvature_hf, which also takes the final value; kappa[i] keeps the
-      // central-difference kappa for cells with no height-function kappa near
-      double khf = __builtin_nan("");
-      const double gx = 0.5 * (phi_seen(d, 2) - phi_seen(d, 1));
-      const double gy = 0.5 * (phi_seen(d, 4) - phi_seen(d, 3));
-      const double gz = 0.5 * (phi_seen(d, 6) - phi_seen(d, 5));
-      const double nrm2 = (gx * gx + gy * gy) + gz * gz;
-      if (nrm2 > 0.0) {
-        const double nrm = sqrt(nrm2);
-        const double nv[3] = {-gx / nrm, -gy / nrm, -gz / nrm};
-        hf_curvature(g, n.x, n.y, n.z, a.flags, a.phi_in, nv, khf);
-      }
-      a.khf[idx] = khf;
-      a.kappa[i] = kap;
-    } else {
-      a.kappa[i] = 3.0 * a.c.sigma * kap;
-    }
+    a.kappa[i] = 3.0 * a.c.sigma * fill_kappa(a, g, idx, n);
   }
 }
 
-// Height-function curvature with plic = 2, after k_curvature: a listed cell
-// takes its own height-function kappa; where its columns are not complete,
-// the mean of those of its D3Q19 interface neighbours that have one (summed
-// in link order: the neighbours lie on the same stretch of surface, while the
-// central-difference kappa of the raw fills is biased by the fill itself);
-// with no such neighbour the central-difference kappa.  kappa[i] = 3 sigma
-// kappa.  Every interface cell is listed, so khf holds this step's value at
-// every interface neighbour.
-__global__ __launch_bounds__(IBLOCK) void k_curvature_hf(SweepArgs a) {
+// Height functions (plic = 2) of the listed interface cells, between the sweep
+// and k_iface: where a cell's nine columns along the axis of its
+// central-difference normal are complete, the normal (else the
+// central-difference one) into the last three values of its aux entry, which
+// k_iface reads and then overwrites, and with surface tension the curvature
+// (else NaN) into khf.  Four lanes per cell, three columns each in three of
+// them; the heights go to all lanes by quad broadcasts.  What bounds it is the
+// latency of the loads, then the work that all lanes of a cell repeat.  256 x
+// 160 x 256 tank, 65,536 cells: a thread per cell that walked its 63 cells one
+// after the other, once here and once more in k_iface, 37 us each time; 16
+// lanes per cell, a column each, 24.5 us; four 20.8 us.
+constexpr int HF_BLOCK = 256;
+constexpr unsigned HF_GRID = 4096;
+
+__global__ __launch_bounds__(HF_BLOCK) void k_columns(SweepArgs a) {
   const Grid g = a.c.grid;
   const int n_i = a.counters[C_I];
-  for (int i = blockIdx.x * IBLOCK + threadIdx.x; i < n_i; i += gridDim.x * IBLOCK) {
+  const int sub = (int)threadIdx.x & (QUAD - 1);
+  const int s3 = min(sub, 2);  // the axis and the columns of this lane (the fourth repeats the third)
+  constexpr int STRIDE = HF_BLOCK / QUAD;
+  for (int i = (int)blockIdx.x * STRIDE + ((int)threadIdx.x / QUAD); i < n_i; i += (int)gridDim.x * STRIDE) {
     const int idx = a.listI[i];
-    double kap = a.khf[idx];
-    if (isnan(kap)) {
-      int x, y, z;
-      coords(g, idx, x, y, z);
-      double sum = 0.0;
-      int cnt = 0;
+    int x, y, z;
+    coords(g, idx, x, y, z);
+    const double phix = a.phi_in[idx];
+    // central difference along the lane's axis of the fill seen from the cell: liquid 1,
+    // gas 0, interface its fill, beyond a wall or in a solid cell the own fill
+    double seen[2];
 #pragma unroll
-      for (int q = 1; q < Q; ++q) {
-        const int s = neighbor(g, x, y, z, CX[q], CY[q], CZ[q]);
-        if (s < 0 || a.flags[s] != IFACE) continue;
-        const double v = a.khf[s];
-        if (isnan(v)) continue;
-        sum = sum + v;
-        ++cnt;
-      }
-      kap = cnt ? sum / (double)cnt : a.kappa[i];
+    for (int h = 0; h < 2; ++h) {
+      const int d = h ? 1 : -1;
+      const int s = neighbor(g, x, y, z, s3 == 0 ? d : 0, s3 == 1 ? d : 0, s3 == 2 ? d : 0);
+      const int sc = s >= 0 ? s : idx;
+      const uint8_t t = a.flags[sc];
+      const double ph = a.phi_in[sc];
+      seen[h] = (s < 0 || t == SOLID) ? phix : (t == LIQ ? 1.0 : (t == GAS ? 0.0 : ph));
     }
-    a.kappa[i] = 3.0 * a.c.sigma * kap;
+    const double gl = 0.5 * (seen[1] - seen[0]);
+    const double gx = qbcast<0>(gl), gy = qbcast<1>(gl), gz = qbcast<2>(gl);
+    const double nrm2 = (gx * gx + gy * gy) + gz * gz;
+    double khf = __builtin_nan("");
+    if (nrm2 > 0.0) {  // the same in all lanes of the quad
+      const double nl = -gl / sqrt(nrm2);
+      double nv[3] = {qbcast<0>(nl), qbcast<1>(nl), qbcast<2>(nl)};
+      const HfAxis A = hf_axis(nv);
+      double hc[3];
+      bool ok = true;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) ok = hf_column(g, x, y, z, A, s3 - 1, j - 1, a.flags, a.phi_in, hc[j]) && ok;
+      if ((((__ballot(ok) >> ((int)__lane_id() & ~(QUAD - 1))) & 7ull) == 7ull)) {
+        const double h[3][3] = {{qbcast<0>(hc[0]), qbcast<0>(hc[1]), qbcast<0>(hc[2])},
+                                {qbcast<1>(hc[0]), qbcast<1>(hc[1]), qbcast<1>(hc[2])},
+                                {qbcast<2>(hc[0]), qbcast<2>(hc[1]), qbcast<2>(hc[2])}};
+        if (a.khf) khf = hf_curvature(h);
+        hf_normal(A, h, nv);
+      }
+      if (sub < 3) a.aux[4 * (size_t)idx + 1 + sub] = sub == 0 ? nv[0] : (sub == 1 ? nv[1] : nv[2]);
+    }
+    if (a.khf && sub == 3) a.khf[idx] = khf;
   }
 }
 
@@ -966,10 +1015,18 @@ hipError_t launch_check_walls(const uint8_t* flags, const Grid& g, const int32_t
   return hipGetLastError();
 }
 
-hipError_t launch_curvature(const StepLaunch& L) {
-  const unsigned nb = std::min<unsigned>(IFACE_GRID, (unsigned)((L.sweep.c.grid.N + IBLOCK - 1) / IBLOCK));
-  k_curvature<<<nb, IBLOCK, 0, (hipStream_t)L.stream>>>(L.sweep);
-  if (L.sweep.c.plic == 2) k_curvature_hf<<<nb, IBLOCK, 0, (hipStream_t)L.stream>>>(L.sweep);
+hipError_t launch_geometry(const StepLaunch& L, int rule) {
+  const SweepArgs& s = L.sweep;
+  if (s.c.plic == 2) {
+    // normals for the FSL rules, curvature for the Laplace pressure
+    if ((rule & 1) || s.c.sigma != 0.0) {
+      const unsigned nb = std::min<unsigned>(HF_GRID, (unsigned)(((size_t)s.c.grid.N * QUAD + HF_BLOCK - 1) / HF_BLOCK));
+      k_columns<<<nb, HF_BLOCK, 0, (hipStream_t)L.stream>>>(s);
+    }
+  } else if (s.c.sigma != 0.0) {
+    const unsigned nb = std::min<unsigned>(IFACE_GRID, (unsigned)((s.c.grid.N + IBLOCK - 1) / IBLOCK));
+    k_curvature<<<nb, IBLOCK, 0, (hipStream_t)L.stream>>>(s);
+  }
   return hipGetLastError();
 }
 

@@ -206,19 +206,23 @@ __device__ __forceinline__ void solid_links(R (&f)[Q], const R (&own)[Q], uint32
 // quotients over s1 in closed form so near-axis normals lose nothing to
 // cancellation.  The offset is found by bisection on [0, 1/2] (54 halvings
 // reach the spacing of doubles there).
+// The quotient of the cell's case is selected first and divided once: as five
+// branches, a wavefront whose cells fall into all of them did four divisions in
+// a row, 54 times over (k_iface of a 256 x 160 x 256 tank, FP32, 65,536
+// interface cells: the bisection 17 -> 12 us; the same values, since base - 0 / 1 is base).
 __device__ __forceinline__ double plic_lower_volume(double al, double s1, double s2, double s3) {
-  if (al <= s1) return (al * al * al) / (6.0 * s1 * s2 * s3);
   const double w = 1.0 / (6.0 * s2 * s3);
   const double base = 3.0 * al * (al - s1) + s1 * s1;
-  if (al <= s2) return base * w;
-  const double r2 = al - s2;
+  const double r2 = al - s2, r3 = al - s3;
   const double s12 = s1 + s2;
-  if (al <= s3) {
-    if (al <= s12) return (base - r2 * r2 * r2 / s1) * w;
-    return (al - 0.5 * s12) / s3;
-  }
-  const double r3 = al - s3;
-  return (base - (r2 * r2 * r2 + r3 * r3 * r3) / s1) * w;
+  const double r2c = r2 * r2 * r2;
+  const bool tip = al <= s1, one = al <= s2, two = al <= s3, flat = two && !(al <= s12);
+  double num = two ? r2c : r2c + r3 * r3 * r3, den = s1;
+  if (flat) num = al - 0.5 * s12, den = s3;
+  if (one) num = 0.0, den = 1.0;
+  if (tip) num = al * al * al, den = 6.0 * s1 * s2 * s3;
+  const double quot = num / den;
+  return (tip || (flat && !one)) ? quot : (base - quot) * w;
 }
 
 // Height-function columns of an interface cell (the second-order
@@ -227,64 +231,83 @@ __device__ __forceinline__ double plic_lower_volume(double al, double s1, double
 // 3 x 3 columns of 7 cells around the cell are summed (liquid 1, gas 0,
 // interface its fill).  With every column complete (fill >= 1 at the liquid
 // end, <= 0 at the gas end, no wall face or solid cell in it) the sums h are
-// the surface heights; sg is the side of the gas along a.  False otherwise.
-__device__ __forceinline__ bool hf_heights(const Grid& g, int x, int y, int z, const uint8_t* __restrict__ flags,
-                                           const double* __restrict__ phi, const double (&nv)[3],
-                                           double (&h)[3][3], int& a, int& sg) {
-  a = 0;
-  if (fabs(nv[1]) > fabs(nv[a])) a = 1;
-  if (fabs(nv[2]) > fabs(nv[a])) a = 2;
-  sg = nv[a] > 0.0 ? 1 : -1;
-  const int e1 = a == 2 ? 0 : a + 1, e2 = a == 0 ? 2 : (a == 1 ? 0 : 1);
-  const int n3[3] = {g.nx, g.ny, g.nz};
-  const int p3[3] = {g.px, g.py, g.pz};
-  const int c0[3] = {x, y, z};
-  for (int i = -1; i <= 1; ++i)
-    for (int j = -1; j <= 1; ++j) {
-      double sum = 0.0;
-      for (int k = -3; k <= 3; ++k) {
-        int d[3];
-        d[a] = k;
-        d[e1] = i;
-        d[e2] = j;
-        int cc[3];
-        for (int b = 0; b < 3; ++b) {
-          int v = c0[b] + d[b];
-          if (v < 0 || v >= n3[b]) {
-            if (!p3[b]) return false;
-            v = ((v % n3[b]) + n3[b]) % n3[b];
-          }
-          cc[b] = v;
-        }
-        const int s = cc[0] + g.nx * (cc[1] + g.ny * cc[2]);
-        const uint8_t t = flags[s];
-        if (t == SOLID) return false;
-        const double v = t == LIQ ? 1.0 : (t == GAS ? 0.0 : phi[s]);
-        if (k == -3 * sg && !(v >= 1.0)) return false;
-        if (k == 3 * sg && !(v <= 0.0)) return false;
-        sum = sum + v;
-      }
-      h[i + 1][j + 1] = sum;
+// the surface heights; sg is the side of the gas along a.
+struct HfAxis {
+  int a, e1, e2, sg;
+};
+
+__device__ __forceinline__ HfAxis hf_axis(const double (&nv)[3]) {
+  HfAxis A;
+  A.a = 0;
+  double big = nv[0];
+  if (fabs(nv[1]) > fabs(big)) A.a = 1, big = nv[1];
+  if (fabs(nv[2]) > fabs(big)) A.a = 2, big = nv[2];
+  A.sg = big > 0.0 ? 1 : -1;
+  A.e1 = A.a == 2 ? 0 : A.a + 1;
+  A.e2 = A.a == 0 ? 2 : (A.a == 1 ? 0 : 1);
+  return A;
+}
+
+// v + d wrapped over a periodic axis of n cells, -1 beyond a wall
+__device__ __forceinline__ int hf_step(int v, int d, int n, int per) {
+  v += d;
+  if (v >= 0 && v < n) return v;
+  return per ? ((v % n) + n) % n : -1;
+}
+
+// The column at offset (i, j) along (e1, e2): its sum into h; true if it is
+// complete.  The cells' loads do not wait for one another.
+__device__ __forceinline__ bool hf_column(const Grid& g, int x, int y, int z, const HfAxis& A, int i, int j,
+                                          const uint8_t* __restrict__ flags, const double* __restrict__ phi,
+                                          double& h) {
+  const int c0 = hf_step(x, A.e1 == 0 ? i : (A.e2 == 0 ? j : 0), g.nx, g.px);
+  const int c1 = hf_step(y, A.e1 == 1 ? i : (A.e2 == 1 ? j : 0), g.ny, g.py);
+  const int c2 = hf_step(z, A.e1 == 2 ? i : (A.e2 == 2 ? j : 0), g.nz, g.pz);
+  bool ok = c0 >= 0 && c1 >= 0 && c2 >= 0;
+  const int n = A.a == 0 ? g.nx : (A.a == 1 ? g.ny : g.nz);
+  const int per = A.a == 0 ? g.px : (A.a == 1 ? g.py : g.pz);
+  const int stride = A.a == 0 ? 1 : (A.a == 1 ? g.nx : g.nx * g.ny);
+  const int at = A.a == 0 ? c0 : (A.a == 1 ? c1 : c2);
+  const int base = c0 + g.nx * (c1 + g.ny * c2) - at * stride;
+  const int own = x + g.nx * (y + g.ny * z);
+  uint8_t t[7];
+  double v[7];
+  int p[7];
+#pragma unroll
+  for (int k = 0; k < 7; ++k) p[k] = at + k - 3;
+  if (at < 3 || at + 3 >= n) {  // near a face
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+      p[k] = hf_step(at, k - 3, n, per);
+      ok = ok && p[k] >= 0;
     }
-  return true;
+  }
+#pragma unroll
+  for (int k = 0; k < 7; ++k) {
+    const int s = ok ? base + p[k] * stride : own;
+    t[k] = flags[s];
+    v[k] = phi[s];
+  }
+  h = 0.0;
+#pragma unroll
+  for (int k = 0; k < 7; ++k) {
+    if (t[k] == SOLID) ok = false;
+    v[k] = t[k] == LIQ ? 1.0 : (t[k] == GAS ? 0.0 : v[k]);
+    h = h + v[k];
+  }
+  const double lo = A.sg > 0 ? v[0] : v[6], hi = A.sg > 0 ? v[6] : v[0];  // liquid end, gas end
+  return ok && lo >= 1.0 && hi <= 0.0;
 }
 
 // Height-function normal: with central differences H_1, H_2 of the column
 // heights across the axis a, nv becomes (s e_a - H_1 e_1 - H_2 e_2)/|.|, s the
 // side of the gas.  Exact for a plane whose slope against a is at most 1.
-// Leaves nv as it is where a column is not complete.
-__device__ __forceinline__ void hf_normal(const Grid& g, int x, int y, int z, const uint8_t* __restrict__ flags,
-                                       const double* __restrict__ phi, double (&nv)[3]) {
-  double h[3][3];
-  int a, sg;
-  if (!hf_heights(g, x, y, z, flags, phi, nv, h, a, sg)) return;
-  const int e1 = a == 2 ? 0 : a + 1, e2 = a == 0 ? 2 : (a == 1 ? 0 : 1);
+__device__ __forceinline__ void hf_normal(const HfAxis& A, const double (&h)[3][3], double (&nv)[3]) {
   const double h1 = 0.5 * (h[2][1] - h[0][1]);
   const double h2 = 0.5 * (h[1][2] - h[1][0]);
   double v[3];
-  v[a] = (double)sg;
-  v[e1] = -h1;
-  v[e2] = -h2;
+#pragma unroll
+  for (int b = 0; b < 3; ++b) v[b] = b == A.a ? (double)A.sg : (b == A.e1 ? -h1 : -h2);
   const double nrm = sqrt((v[0] * v[0] + v[1] * v[1]) + v[2] * v[2]);
   nv[0] = v[0] / nrm;
   nv[1] = v[1] / nrm;
@@ -294,13 +317,8 @@ __device__ __forceinline__ void hf_normal(const Grid& g, int x, int y, int z, co
 // Height-function curvature for the Laplace pressure of Eq. (freeboundary):
 // kappa = -div n = [H_11 (1 + H_2^2) + H_22 (1 + H_1^2) - 2 H_12 H_1 H_2] /
 // (1 + H_1^2 + H_2^2)^(3/2) with central differences of the column heights (a
-// sphere of radius R: -2/R).  Leaves kappa as it is where a column is not
-// complete.
-__device__ __forceinline__ void hf_curvature(const Grid& g, int x, int y, int z, const uint8_t* __restrict__ flags,
-                                          const double* __restrict__ phi, const double (&nv)[3], double& kappa) {
-  double h[3][3];
-  int a, sg;
-  if (!hf_heights(g, x, y, z, flags, phi, nv, h, a, sg)) return;
+// sphere of radius R: -2/R).
+__device__ __forceinline__ double hf_curvature(const double (&h)[3][3]) {
   const double h1 = 0.5 * (h[2][1] - h[0][1]);
   const double h2 = 0.5 * (h[1][2] - h[1][0]);
   const double h11 = (h[2][1] - 2.0 * h[1][1]) + h[0][1];
@@ -308,7 +326,7 @@ __device__ __forceinline__ void hf_curvature(const Grid& g, int x, int y, int z,
   const double h12 = 0.25 * (((h[2][2] - h[2][0]) - h[0][2]) + h[0][0]);
   const double q = (1.0 + h1 * h1) + h2 * h2;
   const double num = (h11 * (1.0 + h2 * h2) + h22 * (1.0 + h1 * h1)) - 2.0 * ((h12 * h1) * h2);
-  kappa = num / (q * sqrt(q));
+  return num / (q * sqrt(q));
 }
 
 __device__ __forceinline__ double plic_plane_offset(double phi, const double (&nv)[3]) {
