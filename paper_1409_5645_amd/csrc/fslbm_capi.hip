@@ -41,6 +41,9 @@ struct fslbm_ctx {
   int rcap = 0;
   bool reorder = false;
   bool list_ok = false;
+  // order 2 (k_together): length of the kept list (null: never), its cell -> entry map
+  int32_t* kept_len = nullptr;
+  int32_t* kept_slot = nullptr;
   // runs of steps in one launch (small lattices): the interface list of that
   // kernel, cell -> entry, its length
   int32_t *res_list = nullptr, *res_slot = nullptr, *res_len = nullptr;
@@ -99,7 +102,7 @@ size_t storage_bytes(int precision) { return precision == FSLBM_FP64 ? 8 : (prec
 
 struct Layout {
   size_t aux, epochs[4], lists[7], counters, scalars, extent, wall_t, kappa, khf, islot, rbuf, rcap, res_list, res_slot, res_len,
-      bars, third, total;
+      kept_len, kept_slot, bars, third, total;
 };
 
 // Entries of the list-ordered population buffer of the interface-first step:
@@ -129,8 +132,9 @@ void wall_table(const fslbm_params& p, double out[6 * Q]) {
 // reorder: room for the interface-first step (cell -> list entry, 19
 // populations of s bytes per list entry); lattices of up to RESIDENT_CELLS
 // also (not in the FP16 form) have the list of the resident step; third: a
-// third population buffer, for the two-step kernel
-Layout layout(size_t N, bool kappa, bool hf, size_t s, bool reorder, bool third) {
+// third population buffer, for the two-step kernel; kept: room for the list
+// that k_together's steps keep (its map is islot's where there is one)
+Layout layout(size_t N, bool kappa, bool hf, size_t s, bool reorder, bool third, bool kept) {
   Layout L{};
   size_t o = 0;
   L.aux = o;
@@ -167,6 +171,10 @@ Layout layout(size_t N, bool kappa, bool hf, size_t s, bool reorder, bool third)
   if (small) o = align_up(o + 4 * N);
   L.res_len = o;
   if (small) o = align_up(o + NCOUNT * sizeof(int32_t));
+  L.kept_len = o;
+  if (kept) o = align_up(o + NCOUNT * sizeof(int32_t));
+  L.kept_slot = reorder ? L.islot : o;
+  if (kept && !reorder) o = align_up(o + 4 * N);
   L.bars = o;
   o = align_up(o + 2 * ALIGN);
   L.third = o;
@@ -293,7 +301,7 @@ fslbm_status fslbm_workspace_size(const fslbm_params* p, size_t* bytes) {
   if (s != FSLBM_OK) { g_init_error = why; return s; }
   if (!bytes) { g_init_error = "bytes is NULL"; return FSLBM_E_INVALID; }
   *bytes = layout((size_t)p->nx * p->ny * p->nz, p->sigma != 0.0, p->plic == 2, storage_bytes(p->precision),
-                  p->precision != FSLBM_FP16S, deep_lattice(*p)).total;
+                  p->precision != FSLBM_FP16S, deep_lattice(*p), true).total;
   return FSLBM_OK;
 }
 
@@ -304,13 +312,13 @@ namespace {
 // fslbm_init with the workspace given separately (the caller's buffer, or the
 // library's static array for fslbm_init_static); parameters already checked.
 fslbm_status init_impl(const fslbm_params* p, const fslbm_buffers* b, void* workspace, size_t workspace_bytes,
-                       bool reorder, bool third, fslbm_ctx** out) {
+                       bool reorder, bool third, bool kept, fslbm_ctx** out) {
   if (!b->f[0] || !b->f[1] || !b->flags || !b->mass || !b->phi[0] || !b->phi[1] || !workspace) {
     g_init_error = "a device buffer is NULL";
     return FSLBM_E_INVALID;
   }
   const size_t N = (size_t)p->nx * p->ny * p->nz;
-  const Layout L = layout(N, p->sigma != 0.0, p->plic == 2, storage_bytes(p->precision), reorder, third);
+  const Layout L = layout(N, p->sigma != 0.0, p->plic == 2, storage_bytes(p->precision), reorder, third, kept);
   if (workspace_bytes < L.total) { g_init_error = "workspace too small"; return FSLBM_E_INVALID; }
   if (((uintptr_t)workspace) % ALIGN) { g_init_error = "workspace not 256-byte aligned"; return FSLBM_E_INVALID; }
 
@@ -373,6 +381,18 @@ fslbm_status init_impl(const fslbm_params* p, const fslbm_buffers* b, void* work
     c->res_slot = (int32_t*)(w + L.res_slot);
     c->res_len = (int32_t*)(w + L.res_len);
   }
+  // The interface cells in the sweep's launch (see TOGETHER_MAX_BYTES), unless
+  // the environment chooses the order or layout of the interface kernel
+  // (FSLBM_TOGETHER=0: never)
+  kept = kept && 2.0 * Q * (double)N * (double)storage_bytes(p->precision) <= TOGETHER_MAX_BYTES &&
+         c->com.incomp && !c->com.stokes;
+  for (const char* name : {"FSLBM_REORDER", "FSLBM_RCAP", "FSLBM_IFACE_QUAD"})
+    if (std::getenv(name)) kept = false;
+  if (const char* e = std::getenv("FSLBM_TOGETHER")) kept = kept && std::atoi(e) != 0;
+  if (kept) {
+    c->kept_len = (int32_t*)(w + L.kept_len);
+    c->kept_slot = (int32_t*)(w + L.kept_slot);
+  }
   c->bars = (unsigned long long*)(w + L.bars);
   {
     double tab[6 * Q];
@@ -432,7 +452,7 @@ fslbm_status fslbm_init(const fslbm_params* p, const fslbm_buffers* b, fslbm_ctx
   if (s != FSLBM_OK) { g_init_error = why; return s; }
   if (!b || !out) { g_init_error = "buffers or out is NULL"; return FSLBM_E_INVALID; }
   // the interface-first buffers: FP32 and FP64 forms (FP16 keeps the other order)
-  s = init_impl(p, b, b->workspace, b->workspace_bytes, p->precision != FSLBM_FP16S, deep_lattice(*p), out);
+  s = init_impl(p, b, b->workspace, b->workspace_bytes, p->precision != FSLBM_FP16S, deep_lattice(*p), true, out);
   if (s != FSLBM_OK) return s;
   fslbm_ctx* c = *out;
   // the two-step kernel's rows shrink by a row for every step since the
@@ -460,7 +480,7 @@ fslbm_status fslbm_init_static(const fslbm_params* p, const fslbm_buffers* b, fs
   if (s != FSLBM_OK) { g_init_error = why; return s; }
   if (!b || !out) { g_init_error = "buffers or out is NULL"; return FSLBM_E_INVALID; }
   const size_t need =
-      layout((size_t)p->nx * p->ny * p->nz, p->sigma != 0.0, p->plic == 2, storage_bytes(p->precision), false, false).total;
+      layout((size_t)p->nx * p->ny * p->nz, p->sigma != 0.0, p->plic == 2, storage_bytes(p->precision), false, false, false).total;
   if (need > (size_t)FSLBM_STATIC_WORKSPACE_BYTES) {
     g_init_error = "the lattice needs " + std::to_string(need) + " bytes of workspace, more than the " +
                    std::to_string((size_t)FSLBM_STATIC_WORKSPACE_BYTES) + " of the static workspace";
@@ -486,7 +506,7 @@ fslbm_status fslbm_init_static(const fslbm_params* p, const fslbm_buffers* b, fs
     ws = g_scratch_ptr[dev];
     g_scratch_busy[dev] = true;
   }
-  s = init_impl(p, b, ws, (size_t)FSLBM_STATIC_WORKSPACE_BYTES, false, false, out);
+  s = init_impl(p, b, ws, (size_t)FSLBM_STATIC_WORKSPACE_BYTES, false, false, false, out);
   std::lock_guard<std::mutex> lock(g_scratch_mu);
   if (s != FSLBM_OK) g_scratch_busy[dev] = false;
   else (*out)->static_device = dev;
@@ -767,6 +787,28 @@ int pair_rows(const fslbm_ctx* c) {
   return yd >= DEEP_ROWS ? yd : 0;
 }
 
+// One step of a run with a kept list (order 2).
+fslbm_status step_together(fslbm_ctx* c, int32_t rule) {
+  StepLaunch L{};
+  step_args(c, L);
+  SweepArgs& s = L.sweep;
+  s.order = L.conv.order = 2;
+  s.len = c->kept_len + C_I;
+  L.conv.islot = c->kept_slot;
+  L.conv.counters_next = c->kept_len;
+  HIPCHK(c, sweep_box(c, s), "extent");
+  HIPCHK(c, launch_together(L, c->p.precision, rule), "step launch");
+  if (!s.freeze) {
+    HIPCHK(c, launch_convert(L, c->p.precision), "conversion launch");
+    c->bar_flip = 1 - c->bar_flip;
+  }
+  c->list_ok = false;
+  c->cur = 1 - c->cur;
+  c->fcur = (c->fcur + 1) % c->nf;
+  c->step += 1;
+  return FSLBM_OK;
+}
+
 // One step; ylow > 0: its sweep leaves the rows y < ylow (to the two-step kernel).
 fslbm_status step_once(fslbm_ctx* c, int32_t rule, int ylow) {
   StepLaunch L{};
@@ -834,6 +876,7 @@ fslbm_status fslbm_step(fslbm_ctx* c, int32_t n, int32_t rule) {
     return FSLBM_E_INVALID;
   }
   const bool resident = c->res_list && !c->timing && !extra_step(c->com);
+  const bool together = c->kept_len && !c->deep && !c->timing && c->quad && n >= TOGETHER_STEPS && !extra_step(c->com);
   int32_t m = 1;  // steps of one pass of the loop
   for (int32_t i = 0; i < n; i += m) {
     if (resident) {
@@ -852,6 +895,15 @@ fslbm_status fslbm_step(fslbm_ctx* c, int32_t n, int32_t rule) {
       continue;
     }
     m = 1;
+    if (together) {
+      if (i % TOGETHER_REBUILD == 0)  // (block counts in the receivers' list, unused between steps)
+        HIPCHK(c, launch_iface_list(c->flags, c->com.grid, c->listR, c->listI, c->kept_slot, c->kept_len + C_I,
+                                    (void*)c->stream), "interface list");
+      fslbm_status st = step_together(c, rule);
+      if (st == FSLBM_OK) st = check_due(c);
+      if (st != FSLBM_OK) return st;
+      continue;
+    }
     const int yd = pair_rows(c);
     if (yd > 0 && n - i >= 2 && (c->check_every <= 0 || (c->step + 1) % c->check_every != 0)) {
       // two steps: the rows below yd at once, into the buffer of the second;

@@ -210,7 +210,7 @@ __device__ __forceinline__ void share_pass(const ConvArgs& a, int step, int32_t*
 // Receivers, and the new cell classes (with the interface kernel first, the
 // new interface cells also join the next list).
 __device__ __forceinline__ void gather_pass(const ConvArgs& a, int step, int nR, int nF, int nEP, int nNI, int nNL,
-                                            unsigned tid, unsigned nth) {
+                                            int len, unsigned tid, unsigned nth) {
   const LinkLane ln;
   for (int e = (int)(tid / CLANES); e < nR; e += (int)(nth / CLANES)) {
     const int r = a.listR[e];
@@ -228,8 +228,14 @@ __device__ __forceinline__ void gather_pass(const ConvArgs& a, int step, int nR,
   const int n1 = nF + nEP, n2 = n1 + nNI, n3 = n2 + nNL;
   for (int j = (int)tid; j < n3; j += (int)nth) {
     const int cell = j < nF ? a.listF[j] : (j < n1 ? a.listEP[j - nF] : (j < n2 ? a.listNI[j - n1] : a.listNL[j - n2]));
-    const bool join = j >= n1;
+    bool join = j >= n1;
     a.flags[cell] = j < nF ? LIQ : (j < n1 ? GAS : IFACE);
+    if (a.order == 2 && join) {
+      // a cell that was on the list (len entries) before has its entry still;
+      // what islot says proves itself, so it needs no first value
+      const unsigned p = (unsigned)a.islot[cell];
+      join = !(p < (unsigned)len && a.listI[p] == cell);
+    }
     if (a.order) {
       const int pos = wave_append_at(join, &a.counters_next[C_I], a.listI, cell);
       if (join) a.islot[cell] = pos;
@@ -246,6 +252,7 @@ template <class F, int BLOCK>
 __device__ __forceinline__ void convert_all(const ConvArgs& v, int step, int nF, int nE, GridBarrier& grid) {
   __shared__ int32_t sc[NCOUNT];
   const unsigned lid = threadIdx.x;
+  const int len = v.order == 2 ? peek(&v.counters_next[C_I]) : 0;  // nothing joins before the last barrier
   if (nF + nE <= SOLO_CELLS) {
     if (blockIdx.x != 0) return;
     if (lid < NCOUNT) sc[lid] = 0;
@@ -256,7 +263,7 @@ __device__ __forceinline__ void convert_all(const ConvArgs& v, int step, int nF,
     share_pass<F, true>(v, step, sc, nF, nEP, nNI, nNL, lid, BLOCK);
     block_meet();
     const int nR = sc[C_R];
-    gather_pass(v, step, nR, nF, nEP, nNI, nNL, lid, BLOCK);
+    gather_pass(v, step, nR, nF, nEP, nNI, nNL, len, lid, BLOCK);
     if (lid == 0) {
       v.counters[C_EP] = nEP;
       v.counters[C_NI] = nNI;
@@ -271,7 +278,7 @@ __device__ __forceinline__ void convert_all(const ConvArgs& v, int step, int nF,
   const int nEP = peek(&v.counters[C_EP]), nNI = peek(&v.counters[C_NI]), nNL = peek(&v.counters[C_NL]);
   share_pass<F, false>(v, step, v.counters, nF, nEP, nNI, nNL, tid, nth);
   grid.meet(false);
-  gather_pass(v, step, peek(&v.counters[C_R]), nF, nEP, nNI, nNL, tid, nth);
+  gather_pass(v, step, peek(&v.counters[C_R]), nF, nEP, nNI, nNL, len, tid, nth);
 }
 
 }  // namespace fslbm

@@ -16,7 +16,6 @@ namespace fslbm {
 constexpr int QBLOCK = 256;               // threads per block
 constexpr int QCELLS = QBLOCK / QUAD;     // cells per block
 constexpr unsigned IFACE4_GRID = 16384;   // blocks at most (grid-stride beyond); a multiple of NXCD
-constexpr int NXCD = 8;                   // XCDs of the device
 
 template <class F, int RULE, bool REC = false>
 __global__ __launch_bounds__(QBLOCK) void k_iface4(SweepArgs a) {
@@ -27,35 +26,7 @@ __global__ __launch_bounds__(QBLOCK) void k_iface4(SweepArgs a) {
 #pragma unroll
     for (int c = 0; c < NCOUNT; ++c) a.counters_next[c] = 0;
   }
-  const QuadLane<typename F::R> ql(g);
-  // Chunks of QCELLS consecutive list entries.  Workgroups go to the eight
-  // XCDs round robin (workgroup b to XCD b mod 8); with a.quad == 2 the chunks
-  // are dealt so that each XCD takes one contiguous stretch of the list, whose
-  // cells share rows and so the lines of their neighbourhoods in that XCD's
-  // L2; else chunk b, b + grid, ...
-  const int nchunk = (n_i + QCELLS - 1) / QCELLS;
-  const bool xcd_order = a.quad == 2;
-  const int per = (nchunk + NXCD - 1) / NXCD;
-  const int k0 = xcd_order ? (int)blockIdx.x / NXCD : (int)blockIdx.x;
-  const int kstride = xcd_order ? (int)gridDim.x / NXCD : (int)gridDim.x;
-  const int kend = xcd_order ? per : nchunk;
-  for (int kk = k0; kk < kend; kk += kstride) {
-    const int chunk = xcd_order ? ((int)blockIdx.x % NXCD) * per + kk : kk;
-    const int i = chunk * QCELLS + ((int)threadIdx.x >> 2);
-    if (chunk >= nchunk || i >= n_i) continue;  // quad-uniform
-    const int idx = a.listI[i];
-    // the list of order 1 comes from the step before: an entry whose cell has
-    // since filled or emptied is skipped (quad-uniform)
-    if (a.order && a.flags[idx] != IFACE) continue;
-    QuadTopo tp;
-    iface4_topo(a, g, ql, idx, tp);
-    bool filled, emptied;
-    iface4_cell<F, RULE, REC>(a, g, ql, tp, a.step, i, idx, filled, emptied);
-    if (!a.freeze) {
-      wave_append(filled, &a.counters[C_F], a.listF, idx);
-      wave_append(emptied, &a.counters[C_E], a.listE, idx);
-    }
-  }
+  iface4_list<F, RULE, REC>(a, g, n_i, QCELLS, (int)blockIdx.x, (int)gridDim.x, a.order != 0);
 }
 
 template <class F, int RULE, bool REC = false>

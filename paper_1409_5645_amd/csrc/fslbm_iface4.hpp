@@ -634,7 +634,7 @@ if ((liqmask >> OPP[kk]) & 1u) {                                                
   // i of rbuf, which the sweep stores with its rows; past rcap, and in
   // order 0, into the cell); the cell's scalars (FP64 bookkeeping) and
   // classification from lane 0
-  const bool to_r = a.order && i < a.rcap;
+  const bool to_r = a.order == 1 && i < a.rcap;
   S* const pb = to_r ? rbuf + i : fout + idx;
   const unsigned ps = to_r ? (unsigned)a.rcap : N;
 #pragma unroll
@@ -663,6 +663,44 @@ if ((liqmask >> OPP[kk]) & 1u) {                                                
       filled = m_new > a.thr_hi * rho;
       emptied = m_new < a.thr_lo * rho;
       if (filled) a.f_epoch[idx] = step;
+    }
+  }
+}
+
+constexpr int NXCD = 8;  // XCDs of the device
+
+// The listed interface cells (n_i of them) by the blocks 0 .. nblocks - 1 of a
+// launch, a quad each, `cells` of them per block.
+// Chunks of `cells` consecutive list entries.  Workgroups go to the eight
+// XCDs round robin (workgroup b to XCD b mod 8); with a.quad == 2 the chunks
+// are dealt so that each XCD takes one contiguous stretch of the list, whose
+// cells share rows and so the lines of their neighbourhoods in that XCD's
+// L2; else chunk b, b + nblocks, ...
+// holes: the list is older than the classes, an entry whose cell has since
+// filled or emptied is skipped.
+template <class F, int RULE, bool REC>
+__device__ __forceinline__ void iface4_list(const SweepArgs& a, const Grid& g, int n_i, int cells, int block,
+                                            int nblocks, bool holes) {
+  const QuadLane<typename F::R> ql(g);
+  const int nchunk = (n_i + cells - 1) / cells;
+  const bool xcd_order = a.quad == 2;
+  const int per = (nchunk + NXCD - 1) / NXCD;
+  const int k0 = xcd_order ? block / NXCD : block;
+  const int kstride = xcd_order ? nblocks / NXCD : nblocks;
+  const int kend = xcd_order ? per : nchunk;
+  for (int kk = k0; kk < kend; kk += kstride) {
+    const int chunk = xcd_order ? (block % NXCD) * per + kk : kk;
+    const int i = chunk * cells + ((int)threadIdx.x >> 2);
+    if (chunk >= nchunk || i >= n_i) continue;  // quad-uniform
+    const int idx = a.listI[i];
+    if (holes && a.flags[idx] != IFACE) continue;  // quad-uniform
+    QuadTopo tp;
+    iface4_topo(a, g, ql, idx, tp);
+    bool filled, emptied;
+    iface4_cell<F, RULE, REC>(a, g, ql, tp, a.step, i, idx, filled, emptied);
+    if (!a.freeze) {
+      wave_append(filled, &a.counters[C_F], a.listF, idx);
+      wave_append(emptied, &a.counters[C_E], a.listE, idx);
     }
   }
 }

@@ -75,7 +75,11 @@ struct SweepArgs {
   // lists the interface cells of time t for the next step (counters_next,
   // islot: cell -> list entry) and leaves the counter zeroing to the
   // interface kernel.
+  // order 2 (k_together): the interface cells in the sweep's own launch, from
+  // the list listI of *len entries (with holes) that the conversions keep.
   int order;
+  const int32_t* len;
+  int nbi;   // order 2: blocks of the launch for the list (set by the launcher)
   int32_t* islot;
   void* rbuf;
   int rcap;
@@ -124,7 +128,8 @@ struct ConvArgs {
   double* reservoir;
   int step;
   // order != 0 (SweepArgs::order): the new interface cells join the list of
-  // the next step (listI, counters_next[C_I], islot)
+  // the next step (listI, counters_next[C_I], islot); 2: unless they are still
+  // on it
   int order;
   int32_t* listI;
   int32_t* islot;
@@ -162,6 +167,22 @@ static_assert(sizeof(ResidentArgs) <= 4096, "kernel arguments");
 // GridBarrier.
 constexpr int RESIDENT_CELLS = 32768;
 constexpr int RESIDENT_STEPS = 256;
+// Where the interface cells and the sweep share a launch (k_together): calls of
+// at least TOGETHER_STEPS steps (the list is built anew for each call, about
+// 20 us, so that classes a caller changed between calls are seen) on lattices
+// whose two population buffers take at most TOGETHER_MAX_BYTES.  Above that the
+// sweep loses by its partly written lines and by the interface cells'
+// scattered traffic what the interface kernel's launch costs (us a step of a
+// tank, separate / together: 40^3 FP64 24.0 / 16.8, FP32 20.6 / 14.5, FP16 23.9
+// / 15.2; 96x72x96 FP64 40.8 / 31.8, FP32 35.9 / 22.1, FP16 36.0 / 22.2;
+// 128x96x128 FP64 81.6 / 70.6, FP32 56.3 / 36.9, FP16 45.4 / 30.1; 160x120x160
+// FP32 78.0 / 71.4, FP16 61.9 / 56.9; 253x159x131 FP16 90.6 / 87.9; 256x160x256
+// FP16 144.8 / 145.4; 512x320x512 FP16 865 / 941).  The list is built anew
+// after TOGETHER_REBUILD steps: cells that have left it stay as holes till
+// then.
+constexpr int TOGETHER_STEPS = 8;
+constexpr int TOGETHER_REBUILD = 64;
+constexpr double TOGETHER_MAX_BYTES = 600e6;
 // Converted cells of a step that one workgroup takes (convert_all): its 16
 // groups of lanes do up to about eight cells and their neighbours in one or
 // two rounds.  101,565-cell tank with about 5 conversions a step (FP32): 29.0 us
@@ -261,6 +282,7 @@ struct AdjArgs {
 };
 
 hipError_t launch_sweep(const StepLaunch& L, int precision, int rule);
+hipError_t launch_together(const StepLaunch& L, int precision, int rule);
 // y and z extent of the fluid cells, and the lowest y of a cell that is not
 // liquid, into ext = (ymin, ymax, zmin, zmax, ynot); (INT_MAX, -1, ..., INT_MAX) if none
 constexpr int EXT_VALUES = 5;

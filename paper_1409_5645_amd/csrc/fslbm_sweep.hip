@@ -2,6 +2,7 @@
 // the populations (Eq. lbe1, lbe2), in one file of its own.  Every other step
 // of the method is in fslbm_kernels.hip.
 #include "fslbm_device.hpp"
+#include "fslbm_iface4.hpp"
 #include "fslbm_internal.hpp"
 #include "fslbm_stencil.hpp"
 
@@ -18,7 +19,9 @@ constexpr int BLOCK = 256;
 // its stores cover whole cache lines: a partly written line costs the memory
 // system more than a whole one.  What it writes into gas cells is not a
 // result (gas populations are never read; a cell that becomes interface is
-// initialised in full).  The interface cells take one of two orders:
+// initialised in full).  The interface cells take one of three orders:
+//   - order 2 (k_together): in the same launch, from a kept list; the sweep
+//     leaves them out;
 //   - order 0: the interface kernel runs after this one and overwrites them
 //     (the FP16 and FP64 forms, a step with walls, surface tension, PLIC,
 //     solids or an adjoint record, or any step with FSLBM_REORDER=0);
@@ -38,18 +41,19 @@ constexpr int BLOCK = 256;
 // loads of a cell are in flight together.  MODEL 1 fixes the incompressible
 // non-Stokes equilibrium at compile time; MODEL 0 reads both switches.
 
-template <class F, int MODEL, bool WITH_U = false, bool ORDER1 = false>
-__global__ __launch_bounds__(BLOCK) void k_sweep(SweepArgs a) {
+template <class F, int MODEL, bool WITH_U, int ORDER>
+__device__ __forceinline__ void sweep_block(const SweepArgs& a, int block) {
   using R = typename F::R;
   using S = typename F::S;
   constexpr bool SH = F::shifted;
+  constexpr bool ORDER1 = ORDER == 1;
   const Grid g = a.c.grid;
-  if (!ORDER1 && blockIdx.x == 0 && threadIdx.x == 0) {
+  if (!ORDER1 && block == 0 && threadIdx.x == 0) {
 #pragma unroll
     for (int i = 0; i < NCOUNT; ++i) a.counters_next[i] = 0;
   }
-  const int brow = (int)blockIdx.x / a.cpr;
-  const int chunk = (int)blockIdx.x - brow * a.cpr;
+  const int brow = block / a.cpr;
+  const int chunk = block - brow * a.cpr;
   const int y = a.box ? a.by0 + brow % a.bny : brow % g.ny;
   const int z = a.box ? a.bz0 + brow / a.bny : brow / g.ny;
   const int row = y + g.ny * z;
@@ -63,7 +67,7 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(SweepArgs a) {
   // 28.4 us)
   const unsigned long long b = __ballot(t == IFACE);
   int pos = -1;
-  if (!ORDER1 || a.shell) {
+  if (ORDER != 2 && (!ORDER1 || a.shell)) {
     pos = block_reserve<BLOCK / 64>(__popcll(b), (ORDER1 ? a.counters_next : a.counters) + C_I) +
           __popcll(b & ((1ull << lane) - 1ull));
     if (t == IFACE) a.listI[pos] = (int)(rbase + x);
@@ -134,8 +138,10 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(SweepArgs a) {
   }
   S* __restrict__ fout = reinterpret_cast<S*>(a.fout);
   if constexpr (!ORDER1) {
+    if (ORDER != 2 || t != IFACE) {
 #pragma unroll
-    for (int q = 0; q < Q; ++q) F::store_raw(fout + ((unsigned)q * N + rbase + (unsigned)x), f[q]);
+      for (int q = 0; q < Q; ++q) F::store_raw(fout + ((unsigned)q * N + rbase + (unsigned)x), f[q]);
+    }
   } else {
     // With the interface kernel first (a wavefront with interface cells has
     // come this far, and every lane of the row but none past its end): the
@@ -172,6 +178,11 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(SweepArgs a) {
       for (int c = 0; c < 3; ++c) __builtin_nontemporal_store(u[c], &uo[(unsigned)c * N + rbase + (unsigned)x]);
     }
   }
+}
+
+template <class F, int MODEL, bool WITH_U = false, bool ORDER1 = false>
+__global__ __launch_bounds__(BLOCK) void k_sweep(SweepArgs a) {
+  sweep_block<F, MODEL, WITH_U, ORDER1 ? 1 : 0>(a, (int)blockIdx.x);
 }
 
 // FP16-storage sweep with two cells per lane (rows of even length; always the
@@ -257,15 +268,15 @@ __device__ __forceinline__ void pull_pair(float (&f0)[Q], float (&f1)[Q], const 
 #undef FSLBM_SHIFT2
 }
 
-template <int MODEL>
-__global__ __launch_bounds__(BLOCK) void k_sweep_h2(SweepArgs a) {
+template <int MODEL, int ORDER>
+__device__ __forceinline__ void sweep_block_h2(const SweepArgs& a, int block) {
   const Grid g = a.c.grid;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  if (block == 0 && threadIdx.x == 0) {
 #pragma unroll
     for (int i = 0; i < NCOUNT; ++i) a.counters_next[i] = 0;
   }
-  const int brow = (int)blockIdx.x / a.cpr;
-  const int chunk = (int)blockIdx.x - brow * a.cpr;
+  const int brow = block / a.cpr;
+  const int chunk = block - brow * a.cpr;
   const int y = a.box ? a.by0 + brow % a.bny : brow % g.ny;
   const int z = a.box ? a.bz0 + brow / a.bny : brow / g.ny;
   const int row = y + g.ny * z;
@@ -277,12 +288,14 @@ __global__ __launch_bounds__(BLOCK) void k_sweep_h2(SweepArgs a) {
   const uint8_t tt[2] = {(uint8_t)(fl2 & 0xffu), (uint8_t)(fl2 >> 8)};
   const int lane = (int)threadIdx.x & 63;
   // interface cells -> list, the first cells of the wavefront's pairs, then the second ones
-  const unsigned long long b0 = __ballot(tt[0] == IFACE), b1 = __ballot(tt[1] == IFACE);
-  const int n0 = __popcll(b0);
-  const int pos = block_reserve<BLOCK / 64>(n0 + __popcll(b1), &a.counters[C_I]);
-  const unsigned long long below = (1ull << lane) - 1ull;
-  if (tt[0] == IFACE) a.listI[pos + __popcll(b0 & below)] = (int)rbase + x0;
-  if (tt[1] == IFACE) a.listI[pos + n0 + __popcll(b1 & below)] = (int)rbase + x0 + 1;
+  if constexpr (ORDER != 2) {
+    const unsigned long long b0 = __ballot(tt[0] == IFACE), b1 = __ballot(tt[1] == IFACE);
+    const int n0 = __popcll(b0);
+    const int pos = block_reserve<BLOCK / 64>(n0 + __popcll(b1), &a.counters[C_I]);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    if (tt[0] == IFACE) a.listI[pos + __popcll(b0 & below)] = (int)rbase + x0;
+    if (tt[1] == IFACE) a.listI[pos + n0 + __popcll(b1 & below)] = (int)rbase + x0 + 1;
+  }
   const bool liq = tt[0] == LIQ || tt[1] == LIQ;
   if (__ballot(liq) == 0) return;  // lanes exchange data below: whole wavefronts only
 
@@ -326,9 +339,53 @@ __global__ __launch_bounds__(BLOCK) void k_sweep_h2(SweepArgs a) {
   if (valid && tt[0] != SOLID && tt[1] != SOLID) {
     char* __restrict__ fo = reinterpret_cast<char*>(a.fout);
     const unsigned o = 2u * (rbase + (unsigned)x0);
+    if constexpr (ORDER != 2) {
 #pragma unroll
-    for (int q = 0; q < Q; ++q) *reinterpret_cast<uint32_t*>(fo + ((unsigned)q * N2 + o)) = h_pack(f0[q], f1[q]);
+      for (int q = 0; q < Q; ++q) *reinterpret_cast<uint32_t*>(fo + ((unsigned)q * N2 + o)) = h_pack(f0[q], f1[q]);
+    } else {
+      // packed before the cells are told apart, so that the conversion is the
+      // one above (fused into the collision's last FMA where that one is)
+      uint32_t pk[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        pk[q] = h_pack(f0[q], f1[q]);
+        asm volatile("" : "+v"(pk[q]));
+      }
+      if (tt[0] != IFACE && tt[1] != IFACE) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) *reinterpret_cast<uint32_t*>(fo + ((unsigned)q * N2 + o)) = pk[q];
+      } else if (tt[0] != IFACE || tt[1] != IFACE) {  // the interface blocks write the other cell of the pair
+        const int hi = tt[0] == IFACE ? 1 : 0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+          *reinterpret_cast<uint16_t*>(fo + ((unsigned)q * N2 + o + 2u * (unsigned)hi)) = (uint16_t)(pk[q] >> (16 * hi));
+      }
+    }
   }
+}
+
+template <int MODEL>
+__global__ __launch_bounds__(BLOCK) void k_sweep_h2(SweepArgs a) {
+  sweep_block_h2<MODEL, 0>(a, (int)blockIdx.x);
+}
+
+// The interface cells and the sweep of a step in one launch (order 2), for
+// lattices that sit in the cache.  Neither reads what the other writes (the
+// sweep leaves the interface cells out), given the list from before the step:
+// the conversions keep it (ConvArgs::order 2), so the sweep builds none and
+// queues at no counter, and the interface kernel's chain of dependent loads
+// runs beside the sweep instead of after it.  The first nbi blocks take the
+// list.  Kernel times apart and together: 61 x 45 x 37 FP64 with the bulk shear
+// 10.2 + 11.8 -> 15.1 us, 128 x 96 x 128 FP32 27.0 + 8.6 -> 28.0 (for the step
+// and the sizes see TOGETHER_MAX_BYTES).
+template <class F, int RULE, bool PAIRS, bool REC>
+__global__ __launch_bounds__(BLOCK) void k_together(SweepArgs a) {
+  if ((int)blockIdx.x < a.nbi) {
+    iface4_list<F, RULE, REC>(a, a.c.grid, *a.len, (int)blockDim.x / QUAD, (int)blockIdx.x, a.nbi, true);
+    return;
+  }
+  if constexpr (PAIRS) sweep_block_h2<1, 2>(a, (int)blockIdx.x - a.nbi);
+  else sweep_block<F, 1, REC, 2>(a, (int)blockIdx.x - a.nbi);
 }
 
 // Extent of the fluid (liquid and interface) cells in y and z, and the lowest
@@ -501,14 +558,70 @@ static void sweep_h2(const StepLaunch& L) {
     k_sweep_h2<0><<<nb, threads, 0, st>>>(a);
 }
 
+// Blocks for the interface list, whose length is on the device: a quad for
+// each of 65,536 cells at once, more in turns
+constexpr unsigned TOGETHER_BLOCKS = 1024;
+
+template <class F, int RULE, bool REC>
+static void together_go(const StepLaunch& L, bool pairs) {
+  SweepArgs a = L.sweep;
+  const Grid& g = a.c.grid;
+  const int per = pairs ? 128 : 64;  // cells of a wavefront
+  const int threads = std::min(BLOCK, 64 * ((g.nx + per - 1) / per));
+  const int cells = threads / 64 * per;
+  a.cpr = (g.nx + cells - 1) / cells;
+  const unsigned nb = (unsigned)a.cpr * (a.box ? (unsigned)a.bny * (unsigned)a.bnz : (unsigned)g.ny * (unsigned)g.nz);
+  const size_t most = REC ? (size_t)a.rec_cap : (size_t)g.N;
+  const unsigned nbi = std::min(TOGETHER_BLOCKS, (unsigned)((most + threads / QUAD - 1) / (threads / QUAD)));
+  a.nbi = (int)((nbi + NXCD - 1) / NXCD * NXCD);
+  hipStream_t st = (hipStream_t)L.stream;
+  if constexpr (std::is_same<F, FormF16>::value) {
+    if (pairs) {
+      k_together<F, RULE, true, REC><<<nb + (unsigned)a.nbi, threads, 0, st>>>(a);
+      return;
+    }
+  }
+  k_together<F, RULE, false, REC><<<nb + (unsigned)a.nbi, threads, 0, st>>>(a);
+}
+
+template <class F>
+static void together_form(const StepLaunch& L, int rule, bool pairs) {
+  if constexpr (!F::scaled) {
+    if (L.sweep.rec_f) {  // a window step (rules 0 and 1)
+      if (rule == 0) together_go<F, 0, true>(L, pairs);
+      else together_go<F, 1, true>(L, pairs);
+      return;
+    }
+  }
+  switch (rule) {
+    case 0: together_go<F, 0, false>(L, pairs); break;
+    case 1: together_go<F, 1, false>(L, pairs); break;
+    case 2: together_go<F, 2, false>(L, pairs); break;
+    case 3: together_go<F, 3, false>(L, pairs); break;
+    case 4: together_go<F, 4, false>(L, pairs); break;
+    default: together_go<F, 5, false>(L, pairs); break;
+  }
+}
+
+static bool pair_rows_fit(const SweepArgs& a) {
+  return a.c.grid.nx % 2 == 0 && a.pairs && !a.c.moving && 38.0 * (double)a.c.grid.N < 4294967296.0;
+}
+
+hipError_t launch_together(const StepLaunch& L, int precision, int rule) {
+  const SweepArgs& a = L.sweep;
+  if (!a.c.incomp || a.c.stokes || !a.len) return hipErrorInvalidValue;  // MODEL 1 only
+  if (precision == 0) together_form<FormF64>(L, rule, false);
+  else if (precision == 1) together_form<FormF32>(L, rule, false);
+  else together_form<FormF16>(L, rule, pair_rows_fit(a));
+  return hipGetLastError();
+}
+
 hipError_t launch_sweep(const StepLaunch& L, int precision, int rule) {
   (void)rule;  // the sweep covers liquid cells only; the rule acts in k_iface
   if (L.sweep.order && precision == 2) return hipErrorInvalidValue;  // FP16 storage: interface kernel after the sweep
   if (precision == 0) sweep_form<FormF64>(L);
   else if (precision == 1) sweep_form<FormF32>(L);
-  else if (L.sweep.c.grid.nx % 2 == 0 && L.sweep.pairs && !L.sweep.c.moving &&
-           38.0 * (double)L.sweep.c.grid.N < 4294967296.0)
-    sweep_h2(L);  // two cells per lane (moving walls take the one-cell form)
+  else if (pair_rows_fit(L.sweep)) sweep_h2(L);  // two cells per lane (moving walls take the one-cell form)
   else sweep_form<FormF16>(L);
   return hipGetLastError();
 }
