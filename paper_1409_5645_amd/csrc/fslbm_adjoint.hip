@@ -672,23 +672,37 @@ __global__ __launch_bounds__(ABLOCK) void k_adj_out(Grid g, const uint8_t* flags
   }
 }
 
-// fixed-order sum of the block partials: out4 = {dL/drho_b, dL/dg}
-__global__ __launch_bounds__(ABLOCK) void k_adj_reduce(const double* ps, int nbs, const double* pi, int nbi,
-                                                       double* out4) {
-  __shared__ double sm[ABLOCK][4];
-  double v[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int b = threadIdx.x; b < nbs; b += ABLOCK)
-    for (int c = 0; c < 3; ++c) v[1 + c] += ps[3 * (size_t)b + c];
-  for (int b = threadIdx.x; b < nbi; b += ABLOCK)
-    for (int c = 0; c < 4; ++c) v[c] += pi[4 * (size_t)b + c];
-  for (int c = 0; c < 4; ++c) sm[threadIdx.x][c] = v[c];
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int c = 0; c < 4; ++c) {
-      double s = 0.0;
-      for (int t = 0; t < ABLOCK; ++t) s += sm[t][c];
-      out4[c] = s;
+// fixed-order sum of the block partials: out4 = {dL/drho_b, dL/dg}; 256 chains
+// per value, a thread each, summed in order.  One block, bound by its chains of
+// loads: 16 of them in flight, a wavefront's threads on one value (128 x 96 x 128,
+// 49,152 slots: 98 us with a thread per four chains and a load at a time, then
+// a thread for the four last sums; RR us).
+constexpr int RCHAINS = 256;
+__global__ __launch_bounds__(4 * RCHAINS) void k_adj_reduce(const double* __restrict__ ps, int nbs,
+                                                            const double* __restrict__ pi, int nbi, double* out4) {
+  __shared__ double sm[4][RCHAINS];
+  const int c = (int)threadIdx.x / RCHAINS, t = (int)threadIdx.x % RCHAINS;
+  double v = 0.0;
+  auto chain = [&](const double* p, int stride, int n) {
+    int b = t;
+    for (; b + 15 * RCHAINS < n; b += 16 * RCHAINS) {
+      double x[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) x[k] = p[(size_t)stride * (size_t)(b + k * RCHAINS)];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v += x[k];
     }
+    for (; b < n; b += RCHAINS) v += p[(size_t)stride * (size_t)b];
+  };
+  if (c > 0) chain(ps + (c - 1), 3, nbs);
+  chain(pi + c, 4, nbi);
+  sm[c][t] = v;
+  __syncthreads();
+  if (t == 0) {
+    double s = 0.0;
+#pragma unroll 16
+    for (int k = 0; k < RCHAINS; ++k) s += sm[c][k];
+    out4[c] = s;
   }
 }
 
@@ -861,7 +875,7 @@ hipError_t launch_adj_out(const Common& c, const uint8_t* flags, int precision, 
 
 hipError_t launch_adj_reduce(const double* part_sweep, int nb_sweep, const double* part_iface, int nb_iface,
                              double* out4, void* stream) {
-  k_adj_reduce<<<1, ABLOCK, 0, (hipStream_t)stream>>>(part_sweep, nb_sweep, part_iface, nb_iface, out4);
+  k_adj_reduce<<<1, 4 * RCHAINS, 0, (hipStream_t)stream>>>(part_sweep, nb_sweep, part_iface, nb_iface, out4);
   return hipGetLastError();
 }
 
