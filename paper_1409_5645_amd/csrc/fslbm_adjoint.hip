@@ -676,7 +676,7 @@ __global__ __launch_bounds__(ABLOCK) void k_adj_out(Grid g, const uint8_t* flags
 // per value, a thread each, summed in order.  One block, bound by its chains of
 // loads: 16 of them in flight, a wavefront's threads on one value (128 x 96 x 128,
 // 49,152 slots: 98 us with a thread per four chains and a load at a time, then
-// a thread for the four last sums; RR us).
+// a thread for the four last sums; 43 us).
 constexpr int RCHAINS = 256;
 __global__ __launch_bounds__(4 * RCHAINS) void k_adj_reduce(const double* __restrict__ ps, int nbs,
                                                             const double* __restrict__ pi, int nbi, double* out4) {
