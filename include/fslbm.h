@@ -228,7 +228,11 @@ fslbm_status fslbm_set_state(fslbm_ctx* c, const double* f, const double* mass, 
  * above), unless fslbm_timing records sweeps or one of the environment
  * variables above, FSLBM_IFACE_QUAD, FSLBM_FP16_PAIRS or FSLBM_RCAP chooses
  * between the kernels of the step-by-step form at init (FSLBM_RESIDENT=0:
- * never); the results are the same bits.  Where the workspace holds a third
+ * never); the results are the same bits.  Larger ones whose two population
+ * buffers take up to 600 MB run the plain steps of a call of eight or more with
+ * the interface cells in the sweep's launch, unless fslbm_timing records sweeps
+ * or FSLBM_REORDER, FSLBM_RCAP or FSLBM_IFACE_QUAD is set at init
+ * (FSLBM_TOGETHER=0: never); the same bits.  Where the workspace holds a third
  * population buffer (fslbm_workspace_size), two steps of a call are taken at
  * once for the rows at the low y end that are liquid throughout, as the extent
  * (measured every 8 steps there) shows, unless fslbm_timing records sweeps or a
