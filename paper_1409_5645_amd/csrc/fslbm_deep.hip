@@ -22,22 +22,22 @@
 // and halo rows run beside one another on one L2.
 //
 // The same operations in the same order as k_sweep: the same bits.
+#include "fslbm_deep_index.hpp"
 #include "fslbm_device.hpp"
 #include "fslbm_internal.hpp"
 #include "fslbm_stencil.hpp"
 
-#include <algorithm>
 #include <type_traits>
 
 namespace fslbm {
 
 template <class F>
 struct DeepTile {
-  static constexpr int TX = sizeof(typename F::S) == 8 ? 32 : 64;
-  static constexpr int TY = sizeof(typename F::S) == 8 ? 12 : 10;
+  static constexpr int TX = deep_tx((int)sizeof(typename F::S));
+  static constexpr int TY = deep_ty((int)sizeof(typename F::S));
   static constexpr int W = TX + 2, H = TY + 2;
   static constexpr int CELLS = W * H;
-  static constexpr int THREADS = TX * H + 64;
+  static constexpr int THREADS = deep_threads((int)sizeof(typename F::S));
   static_assert(2 * H <= 64, "edge cells in one wavefront");
   // planes of the middle state kept, of the links with c_z = 1, 0 and -1
   static constexpr int NP = 3, NZ = 2, NM = 2;
@@ -73,22 +73,13 @@ __global__ __launch_bounds__(DeepTile<F>::THREADS) void k_deep(DeepArgs a) {
   const int y0 = (strip % a.nty) * T::TY;
   const int z0 = (strip / a.nty) * a.zlen, z1 = min(g.nz, z0 + a.zlen);
   const int t = (int)threadIdx.x;
-  // the thread's cell of the halo tile: rows of TX threads, then the two edge
-  // columns.  A thread whose cell lies beyond the lattice (or the rows needed)
-  // works on a cell inside it, for nothing.
-  int hx, hy;
-  if (t < T::TX * T::H) {
-    hy = t / T::TX;
-    hx = 1 + t % T::TX;
-  } else {
-    const int e = min(t - T::TX * T::H, 2 * T::H - 1);
-    hy = e >> 1;
-    hx = (e & 1) ? T::TX + 1 : 0;
-  }
+  // The thread's cell of the halo tile.  A thread whose cell lies beyond the
+  // lattice (or the rows needed) works on a cell inside it, for nothing.
+  const DeepHalo hc = deep_halo(t, T::TX, T::H);
+  const int hx = hc.hx, hy = hc.hy;
   const bool out = hx >= 1 && hx <= T::TX && x0 + hx - 1 < g.nx && hy >= 1 && hy <= T::TY && y0 + hy - 1 < a.yd;
-  int x = x0 + hx - 1;
-  x = x < 0 ? (g.px ? g.nx - 1 : 0) : (x >= g.nx ? (g.px ? x - g.nx : g.nx - 1) : x);
-  const int y = max(0, min(y0 + hy - 1, a.yd));
+  const int x = deep_wrap(x0 + hx - 1, g.nx, g.px);
+  const int y = deep_row(y0 + hy - 1, a.yd);
   const int ci = hy * T::W + hx;
   // in-plane sources
   const int xm = step_axis(x, -1, g.nx, g.px), xp = step_axis(x, 1, g.nx, g.px);
@@ -99,8 +90,7 @@ __global__ __launch_bounds__(DeepTile<F>::THREADS) void k_deep(DeepArgs a) {
   S* __restrict__ fout = reinterpret_cast<S*>(a.fout);
   const Consts<R>& k = pick_consts<R>(a.c);
   R r[Q];
-  // a plane beyond a wall takes the wall's (what it gives is not read)
-  auto plane = [&](int z) __attribute__((always_inline)) -> int { return z < 0 ? (g.pz ? z + g.nz : 0) : (z >= g.nz ? (g.pz ? z - g.nz : g.nz - 1) : z); };
+  auto plane = [&](int z) __attribute__((always_inline)) -> int { return deep_wrap(z, g.nz, g.pz); };
   // a wavefront off the lattice's x and y faces reaches every source at the same
   // distance from its own cell: one lane offset, scalar bases
   const bool inner = __ballot(x == 0 || x == g.nx - 1 || y == 0) == 0ull;
@@ -108,11 +98,9 @@ __global__ __launch_bounds__(DeepTile<F>::THREADS) void k_deep(DeepArgs a) {
   auto load = [&](int z) __attribute__((always_inline)) {  // pulls of plane z
     const int zm = step_axis(z, -1, g.nz, g.pz), zp = step_axis(z, 1, g.nz, g.pz);
     if (inner && (zm | zp) >= 0) {
-      const unsigned om = (unsigned)zm * nxy, o0 = (unsigned)z * nxy, op = (unsigned)zp * nxy;
 #define FSLBM_DPULL(q)                                                                                      \
   {                                                                                                         \
-    const long long b =                                                                                     \
-        (long long)((unsigned)q * N + (CZ[q] == 1 ? om : (CZ[q] == -1 ? op : o0))) - (CX[q] + g.nx * CY[q]); \
+    const long long b = deep_base(q, CX[q], CY[q], CZ[q] == 1 ? zm : (CZ[q] == -1 ? zp : z), g.nx, nxy, N);  \
     r[q] = F::load_raw(reinterpret_cast<const S*>(reinterpret_cast<const char*>(fin + b) + sb));            \
   }
       FSLBM_DPULL(0)
@@ -124,9 +112,7 @@ __global__ __launch_bounds__(DeepTile<F>::THREADS) void k_deep(DeepArgs a) {
     const int sx = CX[q] == 1 ? xm : (CX[q] == -1 ? xp : x);                                        \
     const int sy = CY[q] == 1 ? ym : (CY[q] == -1 ? yp : y);                                        \
     const int sz = CZ[q] == 1 ? zm : (CZ[q] == -1 ? zp : z);                                        \
-    const unsigned o = (sx | sy | sz) < 0 ? (unsigned)OPP[q] * N + (unsigned)z * nxy + self          \
-                                          : (unsigned)q * N + (unsigned)sz * nxy + (unsigned)(sx + g.nx * sy); \
-    r[q] = F::load_raw(fin + o);                                                                    \
+    r[q] = F::load_raw(fin + deep_source(q, OPP[q], sx, sy, sz, x, y, z, (unsigned)g.nx, nxy, N));   \
   }
       FSLBM_DPULL(0)
       FSLBM_LINKS(FSLBM_DPULL)
@@ -217,23 +203,12 @@ __global__ __launch_bounds__(DeepTile<F>::THREADS) void k_deep(DeepArgs a) {
 template <class T, class S, class K>
 static hipError_t deep_go(DeepArgs a, K kernel, hipStream_t st) {
   const Grid& g = a.c.grid;
-  a.ntx = (g.nx + T::TX - 1) / T::TX;
-  a.nty = (a.yd + T::TY - 1) / T::TY;
-  // z chunks: the fewest plane steps of the busiest compute unit
-  long long best = -1;
-  for (int n = 1; n <= std::max(1, g.nz / 8); ++n) {
-    const int len = (g.nz + n - 1) / n;
-    const int chunks = (g.nz + len - 1) / len;
-    const int per = (a.nty * chunks + 7) / 8;
-    const long long rounds = ((long long)per * a.ntx + 31) / 32;
-    const long long cost = rounds * (len + 2);
-    if (best < 0 || cost < best) {
-      best = cost;
-      a.nzc = chunks;
-      a.zlen = len;
-      a.per = per;
-    }
-  }
+  const DeepPlan p = deep_plan(g.nx, g.nz, a.yd, T::TX, T::TY);
+  a.ntx = p.ntx;
+  a.nty = p.nty;
+  a.nzc = p.nzc;
+  a.zlen = p.zlen;
+  a.per = p.per;
   constexpr size_t bytes = (size_t)T::UNITS * T::CELLS * sizeof(S);
   static_assert(bytes <= 160 * 1024, "LDS");
   hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
