@@ -228,7 +228,10 @@ fslbm_status fslbm_set_state(fslbm_ctx* c, const double* f, const double* mass, 
  * above), unless fslbm_timing records sweeps or one of the environment
  * variables above, FSLBM_IFACE_QUAD, FSLBM_FP16_PAIRS or FSLBM_RCAP chooses
  * between the kernels of the step-by-step form at init (FSLBM_RESIDENT=0:
- * never); the results are the same bits.  Larger ones whose two population
+ * never); the results are the same bits.  A kernel whose workgroups wait for one
+ * another (that one, and the conversions of every form) goes on with those of
+ * them that are on the device and never waits for room on it, so any number of
+ * contexts, streams and processes may share a device.  Larger ones whose two population
  * buffers take up to 600 MB run the plain steps of a call of eight or more with
  * the interface cells in the sweep's launch, unless fslbm_timing records sweeps
  * or FSLBM_REORDER, FSLBM_RCAP or FSLBM_IFACE_QUAD is set at init

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "../../include/fslbm.h"
+#include "fslbm_barrier.hpp"
 #include "fslbm_internal.hpp"
 
 using namespace fslbm;
@@ -47,10 +48,13 @@ struct fslbm_ctx {
   // runs of steps in one launch (small lattices): the interface list of that
   // kernel, cell -> entry, its length
   int32_t *res_list = nullptr, *res_slot = nullptr, *res_len = nullptr;
-  // barrier words of the kernels whose workgroups meet: a launch counts in one
-  // and zeroes the other for the next
+  // words of the kernels whose workgroups meet: a launch counts in one set and
+  // zeroes the other for the next
   unsigned long long* bars = nullptr;
   int bar_flip = 0;
+  // workgroups of a team at most (FSLBM_TEAM) and looks before it is closed
+  // (FSLBM_TEAM_WAIT): see fslbm_barrier.hpp; for tests of the smaller teams
+  int team = 1 << 20, team_wait = TEAM_WAIT;
   double* reservoir;
   double* kappa = nullptr;  // surface tension only
   double* khf = nullptr;    // surface tension with plic = 2 only
@@ -394,6 +398,8 @@ fslbm_status init_impl(const fslbm_params* p, const fslbm_buffers* b, void* work
     c->kept_slot = (int32_t*)(w + L.kept_slot);
   }
   c->bars = (unsigned long long*)(w + L.bars);
+  if (const char* e = std::getenv("FSLBM_TEAM")) c->team = std::max(1, std::atoi(e));
+  if (const char* e = std::getenv("FSLBM_TEAM_WAIT")) c->team_wait = std::max(0, std::min(TEAM_WAIT, std::atoi(e)));
   {
     double tab[6 * Q];
     wall_table(*p, tab);
@@ -727,6 +733,8 @@ void step_args(const fslbm_ctx* c, StepLaunch& L) {
   v.counters_next = s.counters_next;
   v.bar = c->bars + c->bar_flip * (ALIGN / sizeof(unsigned long long));
   v.bar_next = c->bars + (1 - c->bar_flip) * (ALIGN / sizeof(unsigned long long));
+  v.team = c->team;
+  v.team_wait = c->team_wait;
   s.islot = c->islot;
   s.rbuf = c->rbuf;
   s.rcap = c->rcap;
@@ -763,6 +771,8 @@ hipError_t resident_steps(fslbm_ctx* c, int m, int32_t rule) {
   r.len = c->res_len;
   r.bar = L.conv.bar;
   r.bar_next = L.conv.bar_next;
+  r.team = c->team;
+  r.team_wait = c->team_wait;
   r.step = c->step;
   r.n = m;
   const hipError_t e = launch_resident(r, c->p.precision, rule, (void*)c->stream);

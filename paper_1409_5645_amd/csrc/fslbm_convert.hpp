@@ -243,10 +243,10 @@ __device__ __forceinline__ void gather_pass(const ConvArgs& a, int step, int nR,
   }
 }
 
-// All the conversions of a step by the threads of a grid, after its lists F and
+// All the conversions of a step by the threads of a team, after its lists F and
 // E are complete and visible (nF, nE their lengths, the same in every thread).
 // Up to SOLO_CELLS converted cells the first workgroup does them alone, the
-// others pass: its barriers are cheap, those of the grid (and its atomics,
+// others pass: its barriers are cheap, those of the team (and its atomics,
 // which leave the L2) are not.
 template <class F, int BLOCK>
 __device__ __forceinline__ void convert_all(const ConvArgs& v, int step, int nF, int nE, GridBarrier& grid) {
@@ -254,7 +254,7 @@ __device__ __forceinline__ void convert_all(const ConvArgs& v, int step, int nF,
   const unsigned lid = threadIdx.x;
   const int len = v.order == 2 ? peek(&v.counters_next[C_I]) : 0;  // nothing joins before the last barrier
   if (nF + nE <= SOLO_CELLS) {
-    if (blockIdx.x != 0) return;
+    if (grid.team.rank != 0u) return;
     if (lid < NCOUNT) sc[lid] = 0;
     __syncthreads();
     mark_pass<true>(v, step, sc, nF, nE, lid, BLOCK);
@@ -272,7 +272,7 @@ __device__ __forceinline__ void convert_all(const ConvArgs& v, int step, int nF,
     }
     return;
   }
-  const unsigned tid = blockIdx.x * BLOCK + lid, nth = gridDim.x * BLOCK;
+  const unsigned tid = grid.team.rank * BLOCK + lid, nth = grid.team.size * BLOCK;
   mark_pass<false>(v, step, v.counters, nF, nE, tid, nth);
   grid.meet(false);
   const int nEP = peek(&v.counters[C_EP]), nNI = peek(&v.counters[C_NI]), nNL = peek(&v.counters[C_NL]);

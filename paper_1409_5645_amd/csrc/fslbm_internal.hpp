@@ -134,8 +134,9 @@ struct ConvArgs {
   int32_t* listI;
   int32_t* islot;
   int32_t* counters_next;
-  unsigned long long* bar;       // barrier word, zero
-  unsigned long long* bar_next;  // barrier word of the next launch (zeroed by this one)
+  unsigned long long* bar;       // barrier and team words, zero
+  unsigned long long* bar_next;  // those of the next launch (zeroed by this one)
+  int team, team_wait;           // most workgroups of a team and how long it stays open (fslbm_barrier.hpp)
 };
 
 struct StepLaunch {
@@ -154,8 +155,9 @@ struct ResidentArgs {
   int32_t* list;   // interface cells, 2 N entries
   int32_t* islot;  // cell -> its entry
   int32_t* len;    // NCOUNT values, [C_I] the length of the list
-  unsigned long long* bar;       // barrier word, zero
-  unsigned long long* bar_next;  // barrier word of the next launch (zeroed by this one)
+  unsigned long long* bar;       // as in ConvArgs
+  unsigned long long* bar_next;
+  int team, team_wait;
   int step, n;
 };
 static_assert(sizeof(ResidentArgs) <= 4096, "kernel arguments");

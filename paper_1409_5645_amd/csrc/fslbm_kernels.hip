@@ -596,17 +596,24 @@ __global__ __launch_bounds__(HF_BLOCK) void k_columns(SweepArgs a) {
 // most steps convert no cell or a few.  As three kernels of one thread per cell
 // and link they took 5.8 us of a step without conversions and 17 us with five
 // converted cells (101,565-cell tank, FP64); now 1.7 and about 8 us.
-// 512 groups of lanes (see convert_all) on an eighth of the compute units (the
-// workgroups wait for one another: see fslbm_barrier.hpp)
+// 512 groups of lanes (see convert_all) on an eighth of the compute units, as
+// far as they are on the device (the workgroups wait for one another: see
+// fslbm_barrier.hpp)
 constexpr int CBLOCK = 512;
 constexpr unsigned CGRID = 32;
 
 template <class F>
 __global__ __launch_bounds__(CBLOCK) void k_convert(ConvArgs a) {
-  GridBarrier grid(a.bar);
-  if (blockIdx.x == 0 && threadIdx.x == 0) *a.bar_next = 0ull;
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.bar_next[0] = a.bar_next[TEAM_WORD] = 0ull;
   const int nF = a.counters[C_F], nE = a.counters[C_E];
-  if (nF + nE > 0) convert_all<F, CBLOCK>(a, a.step, nF, nE, grid);
+  if (nF + nE == 0) return;
+  Team team{blockIdx.x, 1u};
+  if (nF + nE > SOLO_CELLS) {
+    team = join_team(a.bar + TEAM_WORD, min((unsigned)a.team, gridDim.x), a.team_wait, [] {});
+    if (team.size == 0u) return;
+  }
+  GridBarrier grid(a.bar, team);
+  convert_all<F, CBLOCK>(a, a.step, nF, nE, grid);
 }
 
 // The interface cells of the current classes into list and islot (cell -> list

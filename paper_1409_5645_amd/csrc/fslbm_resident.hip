@@ -22,13 +22,11 @@
 
 namespace fslbm {
 
-// Threads and workgroups.  The workgroups wait for one another, so all of them
-// have to be on the device at once: at most 16384 threads (a 512-thread
-// workgroup takes one of the 256 compute units, or part of it), so that eight
-// such kernels fit beside one another; more did not help lattices of this size
-// (12,000 cells: 9.9 us a step with 32 workgroups and with 64).  The FP64
-// kernels with a boundary shear from the bulk take smaller workgroups, whose
-// threads may hold the 350 registers they need.
+// Threads and workgroups: at most 16384 threads; more did not help lattices of
+// this size (12,000 cells: 9.9 us a step with 32 workgroups and with 64).  The
+// FP64 kernels with a boundary shear from the bulk take smaller workgroups,
+// whose threads may hold the 350 registers they need: a compute unit each.  How
+// many of them are on the device at once is found out by the kernel (join_team).
 constexpr int RTHREADS = 16384;
 template <class F, int RULE>
 constexpr int rblock() {
@@ -85,9 +83,16 @@ __global__ __launch_bounds__((rblock<F, RULE>())) void k_resident(ResidentArgs r
   const Grid g = r.sweep[0].c.grid;
   const uint8_t* flags = r.sweep[0].flags;
   const QuadLane<typename F::R> ql(g);
-  const int tid = (int)(blockIdx.x * RBLOCK + threadIdx.x), nth = (int)(gridDim.x * RBLOCK);
-  GridBarrier grid(r.bar);
-  if (tid == 0) *r.bar_next = 0ull;
+  if (blockIdx.x == 0 && threadIdx.x == 0) r.bar_next[0] = r.bar_next[TEAM_WORD] = 0ull;
+  const Team team = join_team(r.bar + TEAM_WORD, min((unsigned)r.team, gridDim.x), r.team_wait, [&] {
+    __hip_atomic_store(&r.len[C_I], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  });
+  if (team.size == 0u) return;
+  GridBarrier grid(r.bar, team);
+  const int tid = (int)team.rank * RBLOCK + (int)threadIdx.x, nth = (int)team.size * RBLOCK;
+  const int wave = __builtin_amdgcn_readfirstlane(tid);  // the wavefront's first thread
+  // threads for interface cells at most: half of the workgroups, or of the only one
+  const int most = team.size > 1u ? (int)(team.size / 2u) * RBLOCK : RBLOCK / 2;
   int len = 0;
   bool rebuild = true;
   // The cell a thread works on and where it pulls from, kept from step to step
@@ -99,9 +104,11 @@ __global__ __launch_bounds__((rblock<F, RULE>())) void k_resident(ResidentArgs r
   unsigned off[Q];
   for (int t = 0; t < r.n; ++t) {
     if (rebuild) {  // the interface cells of the current classes (uniform over the grid)
-      if (t > 0) grid.meet(false);  // every workgroup has read the old length
-      if (tid == 0) __hip_atomic_store(&r.len[C_I], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      grid.meet(false);
+      if (t > 0) {
+        grid.meet(false);  // every workgroup has read the old length
+        if (tid == 0) __hip_atomic_store(&r.len[C_I], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        grid.meet(false);
+      }
       for (int i0 = 0; i0 < g.N; i0 += nth) {
         const int i = i0 + tid;
         const bool it = i < g.N && flags[i] == IFACE;
@@ -118,10 +125,10 @@ __global__ __launch_bounds__((rblock<F, RULE>())) void k_resident(ResidentArgs r
     if (tid < NCOUNT) a.counters_next[tid] = 0;
     // the interface cells to the first workgroups, four lanes each, the others
     // the liquid cells
-    const int nbi = min((4 * len + RBLOCK - 1) / RBLOCK, (int)gridDim.x / 2);
+    const int ni = min((QUAD * len + RBLOCK - 1) / RBLOCK * RBLOCK, most);
     bool conv = false;
-    if ((int)blockIdx.x < nbi) {
-      const int stride = nbi * (RBLOCK / QUAD);
+    if (wave < ni) {
+      const int stride = ni / QUAD;
       for (int i = tid >> 2; i < len; i += stride) {
         if (changed || len > stride) {
           idx = r.list[i];
@@ -139,8 +146,8 @@ __global__ __launch_bounds__((rblock<F, RULE>())) void k_resident(ResidentArgs r
         }
       }
     } else {
-      const int first = tid - nbi * RBLOCK, stride = nth - nbi * RBLOCK;
-      for (int i = first; i < g.N; i += stride) {
+      const int stride = nth - ni;
+      for (int i = tid - ni; i < g.N; i += stride) {
         if (changed || g.N > stride) {
           idx = flags[i] == LIQ ? i : -1;
           if (idx >= 0) pull_offsets(g, idx, off);
