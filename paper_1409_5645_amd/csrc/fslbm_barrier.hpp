@@ -103,7 +103,7 @@ struct GridBarrier {
     }
     __syncthreads();
     const unsigned now = (unsigned)(got >> (odd ? 48 : 32)) & 0xffffu;
-    const bool raised = now != (odd ? seen1 : seen0);
+    const bool raised = __builtin_amdgcn_readfirstlane((int)(now != (odd ? seen1 : seen0))) != 0;
     seen0 = odd ? seen0 : now;
     seen1 = odd ? now : seen1;
     odd = !odd;

@@ -19,7 +19,8 @@
 // unrolled code, the passes took 8, 5 and 4 us for five converted cells.)
 //
 // A few converted cells are left to one workgroup (SOLO: list lengths in LDS,
-// atomics that need not leave its L2), many are spread over the grid.
+// atomics that need not leave its L2), many are spread over a team of
+// workgroups (convert_team).
 #pragma once
 
 #include "fslbm_barrier.hpp"
@@ -76,27 +77,73 @@ __device__ __forceinline__ T cell_lane(T v, int i) {
 // new_epoch's step stamps go to gas and liquid cells only.
 __device__ __forceinline__ int ep_stamp(int step) { return -2 - step; }
 
-template <bool SOLO>
-__device__ __forceinline__ void mark_pass(const ConvArgs& a, int step, int32_t* cnt, int nF, int nE, unsigned tid,
-                                          unsigned nth) {
+// value[l] into list l (of L, whose counters are neighbours in cnt) for the lanes
+// with pred[l] set.  BLOCK = 0: an atomic per wavefront and list; else one for the
+// workgroup of BLOCK threads, the lists' at once, which every thread calls: the
+// device serves atomics on one address one after another, and with one per
+// wavefront a surface that converts as a whole queued there.
+template <int BLOCK, int L>
+__device__ __forceinline__ void append_to(const bool (&pred)[L], int32_t* cnt, int32_t* const (&list)[L], const int (&value)[L]) {
+  if constexpr (BLOCK == 0) {
+#pragma unroll
+    for (int l = 0; l < L; ++l) wave_append(pred[l], &cnt[l], list[l], value[l]);
+  } else {
+    constexpr int WAVES = BLOCK / 64;
+    __shared__ int32_t n[L][WAVES], first[L];
+    const int w = (int)threadIdx.x >> 6, lane = (int)threadIdx.x & 63;
+    unsigned long long b[L];
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+      b[l] = __ballot(pred[l]);
+      if (lane == 0) n[l][w] = __popcll(b[l]);
+    }
+    __syncthreads();
+    if (threadIdx.x < L) {
+      int total = 0;
+#pragma unroll
+      for (int v = 0; v < WAVES; ++v) total += n[threadIdx.x][v];
+      first[threadIdx.x] = total ? atomicAdd(&cnt[threadIdx.x], total) : 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+      if (!pred[l]) continue;
+      int at = first[l] + __popcll(b[l] & ((1ull << lane) - 1ull));
+#pragma unroll
+      for (int v = 0; v < WAVES; ++v) at += v < w ? n[l][v] : 0;
+      list[l][at] = value[l];
+    }
+    __syncthreads();  // (the next round's counts)
+  }
+}
+
+// The passes: `first` is the workgroup's first group of lanes in the team,
+// `groups` the team's; every workgroup's threads go through the same rounds.
+// SOLO: one workgroup alone; BLOCK: see append_to.
+template <bool SOLO, int BLOCK>
+__device__ __forceinline__ void mark_pass(const ConvArgs& a, int step, int32_t* cnt, int nF, int nE, int first,
+                                          int groups) {
   const Grid& g = a.c.grid;
   const LinkLane ln;
-  for (unsigned e = tid / CLANES; e < (unsigned)(nF + nE); e += nth / CLANES) {
-    const bool filled = e < (unsigned)nF;
-    const int c = filled ? a.listF[e] : a.listE[e - (unsigned)nF];
-    const int s = ln.neighbour(g, c);
+  const int n = nF + nE;
+  static_assert(C_NI == C_EP + 1 && C_NL == C_EP + 2, "lists marked here");
+  int32_t* const lists[3] = {a.listEP, a.listNI, a.listNL};
+  const int mine = (int)threadIdx.x / CLANES;
+  for (int e0 = first; e0 + (BLOCK == 0 ? mine : 0) < n; e0 += groups) {
+    const int e = e0 + mine;
+    const bool on = BLOCK == 0 || e < n, filled = e < nF;
+    const int c = !on ? 0 : (filled ? a.listF[e] : a.listE[e - nF]);
+    const int s = on ? ln.neighbour(g, c) : -1;
     const uint8_t ts = s >= 0 ? a.flags[s] : (uint8_t)SOLID;
     const int fe = s >= 0 ? a.f_epoch[s] : -1;
     // E' = E minus N(F)
     const bool drop = !filled && cell_ballot(fe == step) != 0u;
-    const bool ep = !filled && !drop;
+    const bool ep = on && !filled && !drop;
     if (ep && ln.q == 0) a.new_epoch[c] = ep_stamp(step);
-    wave_append(ep && ln.q == 0, &cnt[C_EP], a.listEP, c);
     // Which lane wins a new cell's mark does not change the result
     bool win = false;
-    if (filled ? ts == GAS : (ep && ts == LIQ)) win = exchange<SOLO>(&a.new_epoch[s], step) != step;
-    wave_append(win && filled, &cnt[C_NI], a.listNI, s);
-    wave_append(win && !filled, &cnt[C_NL], a.listNL, s);
+    if (on && (filled ? ts == GAS : (ep && ts == LIQ))) win = exchange<SOLO>(&a.new_epoch[s], step) != step;
+    append_to<BLOCK>({ep && ln.q == 0, win && filled, win && !filled}, cnt + C_EP, lists, {c, s, s});
   }
 }
 
@@ -111,11 +158,11 @@ __device__ __forceinline__ bool iface_after(const ConvArgs& a, int step, int t) 
 }
 
 // Excess of a converted cell c: split over its eligible neighbours (or handed
-// to the reservoir), which are listed as receivers.
+// to the reservoir).  Whether the lane's neighbour s is a receiver not yet listed.
 template <bool SOLO>
-__device__ __forceinline__ void share_cell(const ConvArgs& a, int step, int32_t* cnt, const LinkLane& ln, int c,
-                                           bool filled) {
-  const int s = ln.neighbour(a.c.grid, c);
+__device__ __forceinline__ bool share_cell(const ConvArgs& a, int step, const LinkLane& ln, int c, bool filled,
+                                           int& s) {
+  s = ln.neighbour(a.c.grid, c);
   const bool el = (s >= 0) & iface_after(a, step, s >= 0 ? s : c);
   const double m = a.mass[c], r = a.aux[4 * (size_t)c];
   const int n_elig = __popc(cell_ballot(el));
@@ -129,9 +176,7 @@ __device__ __forceinline__ void share_cell(const ConvArgs& a, int step, int32_t*
       a.conv_epoch[c] = step;
     }
   }
-  bool first = false;
-  if (el) first = exchange<SOLO>(&a.recv_epoch[s], step) != step;
-  wave_append(first, &cnt[C_R], a.listR, s);
+  return el && exchange<SOLO>(&a.recv_epoch[s], step) != step;
 }
 
 // New interface cell from gas: f = f^eq of the mean collision density and
@@ -195,15 +240,21 @@ __device__ __forceinline__ void init_from_liquid(const ConvArgs& a, const LinkLa
   }
 }
 
-template <class F, bool SOLO>
+template <class F, bool SOLO, int BLOCK>
 __device__ __forceinline__ void share_pass(const ConvArgs& a, int step, int32_t* cnt, int nF, int nEP, int nNI,
-                                           int nNL, unsigned tid, unsigned nth) {
+                                           int nNL, int first, int groups) {
   const LinkLane ln;
   const int n0 = nF + nEP, n1 = n0 + nNI, n2 = n1 + nNL;
-  for (int e = (int)(tid / CLANES); e < n2; e += (int)(nth / CLANES)) {
-    if (e < n0) share_cell<SOLO>(a, step, cnt, ln, e < nF ? a.listF[e] : a.listEP[e - nF], e < nF);
+  int32_t* const lists[1] = {a.listR};
+  const int mine = (int)threadIdx.x / CLANES;
+  for (int e0 = first; e0 + (BLOCK == 0 ? mine : 0) < n2; e0 += groups) {
+    const int e = e0 + mine;
+    bool recv = false;
+    int s = -1;
+    if (e < n0) recv = share_cell<SOLO>(a, step, ln, e < nF ? a.listF[e] : a.listEP[e - nF], e < nF, s);
     else if (e < n1) init_from_gas<F>(a, ln, a.listNI[e - n0]);
-    else init_from_liquid<F>(a, ln, a.listNL[e - n1]);
+    else if (e < n2) init_from_liquid<F>(a, ln, a.listNL[e - n1]);
+    if (BLOCK == 0 || e0 < n0) append_to<BLOCK>({recv}, cnt + C_R, lists, {s});
   }
 }
 
@@ -247,20 +298,22 @@ __device__ __forceinline__ void gather_pass(const ConvArgs& a, int step, int nR,
 // E are complete and visible (nF, nE their lengths, the same in every thread).
 // Up to SOLO_CELLS converted cells the first workgroup does them alone, the
 // others pass: its barriers are cheap, those of the team (and its atomics,
-// which leave the L2) are not.
-template <class F, int BLOCK>
+// which leave the L2) are not.  WIDE: lists by one atomic per workgroup, for
+// teams that may do many cells.
+template <class F, int BLOCK, bool WIDE>
 __device__ __forceinline__ void convert_all(const ConvArgs& v, int step, int nF, int nE, GridBarrier& grid) {
   __shared__ int32_t sc[NCOUNT];
+  constexpr int GROUPS = BLOCK / CLANES;
   const unsigned lid = threadIdx.x;
   const int len = v.order == 2 ? peek(&v.counters_next[C_I]) : 0;  // nothing joins before the last barrier
   if (nF + nE <= SOLO_CELLS) {
     if (grid.team.rank != 0u) return;
     if (lid < NCOUNT) sc[lid] = 0;
     __syncthreads();
-    mark_pass<true>(v, step, sc, nF, nE, lid, BLOCK);
+    mark_pass<true, 0>(v, step, sc, nF, nE, 0, GROUPS);
     block_meet();
     const int nEP = sc[C_EP], nNI = sc[C_NI], nNL = sc[C_NL];
-    share_pass<F, true>(v, step, sc, nF, nEP, nNI, nNL, lid, BLOCK);
+    share_pass<F, true, 0>(v, step, sc, nF, nEP, nNI, nNL, 0, GROUPS);
     block_meet();
     const int nR = sc[C_R];
     gather_pass(v, step, nR, nF, nEP, nNI, nNL, len, lid, BLOCK);
@@ -273,10 +326,11 @@ __device__ __forceinline__ void convert_all(const ConvArgs& v, int step, int nF,
     return;
   }
   const unsigned tid = grid.team.rank * BLOCK + lid, nth = grid.team.size * BLOCK;
-  mark_pass<false>(v, step, v.counters, nF, nE, tid, nth);
+  const int first = (int)grid.team.rank * GROUPS, groups = (int)grid.team.size * GROUPS;
+  mark_pass<false, WIDE ? BLOCK : 0>(v, step, v.counters, nF, nE, first, groups);
   grid.meet(false);
   const int nEP = peek(&v.counters[C_EP]), nNI = peek(&v.counters[C_NI]), nNL = peek(&v.counters[C_NL]);
-  share_pass<F, false>(v, step, v.counters, nF, nEP, nNI, nNL, tid, nth);
+  share_pass<F, false, WIDE ? BLOCK : 0>(v, step, v.counters, nF, nEP, nNI, nNL, first, groups);
   grid.meet(false);
   gather_pass(v, step, peek(&v.counters[C_R]), nF, nEP, nNI, nNL, len, tid, nth);
 }

@@ -596,11 +596,21 @@ __global__ __launch_bounds__(HF_BLOCK) void k_columns(SweepArgs a) {
 // most steps convert no cell or a few.  As three kernels of one thread per cell
 // and link they took 5.8 us of a step without conversions and 17 us with five
 // converted cells (101,565-cell tank, FP64); now 1.7 and about 8 us.
-// 512 groups of lanes (see convert_all) on an eighth of the compute units, as
-// far as they are on the device (the workgroups wait for one another: see
-// fslbm_barrier.hpp)
+//
+// Workgroups of 16 groups of lanes; how many of the grid's take part follows the
+// number of converted cells, between what a barrier costs (about 18 ns per
+// workgroup, three in a launch) and the rounds a pass then needs.  A step of
+// which that many cells of a flat surface fill (512 x 20 x 512 FP16 / 61 x 45 x 37
+// FP64, us, three kernels / 32 workgroups / this rule): 9 cells 136 / 121 / 119,
+// 50 / 49 / 48; 50: 147 / 122 / 122, 54 / 52 / 48; 500: 148 / 151 / 134, 56 / 66
+// / 58; 2,000: 163 / 245 / 170, 60 / 78 / 65; 5,000: 207 / 435 / 229; 20,000: 415
+// / 1,190 / 397; 262,144: 1,188 / 3,809 / 800.
 constexpr int CBLOCK = 512;
-constexpr unsigned CGRID = 32;
+constexpr unsigned CGRID = 256;
+
+__device__ __forceinline__ unsigned convert_team(unsigned cells) {
+  return max(min(max(cells / 4u, 32u), 96u), min(cells / 20u, CGRID));
+}
 
 template <class F>
 __global__ __launch_bounds__(CBLOCK) void k_convert(ConvArgs a) {
@@ -609,11 +619,15 @@ __global__ __launch_bounds__(CBLOCK) void k_convert(ConvArgs a) {
   if (nF + nE == 0) return;
   Team team{blockIdx.x, 1u};
   if (nF + nE > SOLO_CELLS) {
-    team = join_team(a.bar + TEAM_WORD, min((unsigned)a.team, gridDim.x), a.team_wait, [] {});
+    const unsigned most = min((unsigned)a.team, convert_team((unsigned)(nF + nE)));
+    if (blockIdx.x >= most) return;
+    team = join_team(a.bar + TEAM_WORD, most, a.team_wait, [] {});
     if (team.size == 0u) return;
+  } else if (blockIdx.x != 0u) {
+    return;
   }
   GridBarrier grid(a.bar, team);
-  convert_all<F, CBLOCK>(a, a.step, nF, nE, grid);
+  convert_all<F, CBLOCK, true>(a, a.step, nF, nE, grid);
 }
 
 // The interface cells of the current classes into list and islot (cell -> list

@@ -157,7 +157,7 @@ __global__ __launch_bounds__((rblock<F, RULE>())) void k_resident(ResidentArgs r
     }
     changed = false;
     if (grid.meet(conv)) {
-      convert_all<F, RBLOCK>(v, step, peek(&a.counters[C_F]), peek(&a.counters[C_E]), grid);
+      convert_all<F, RBLOCK, false>(v, step, peek(&a.counters[C_F]), peek(&a.counters[C_E]), grid);
       grid.meet(false);
       len = peek(&r.len[C_I]);
       rebuild = len > g.N;
