@@ -225,10 +225,13 @@ fslbm_status fslbm_set_state(fslbm_ctx* c, const double* f, const double* mass, 
  * the FP32 and FP64 forms; FP16 storage always runs the interface kernel
  * after the sweep.  On lattices of up to 32,768 cells the plain step of the
  * FP32 and FP64 forms runs in one launch of up to 256 steps (without the wait
- * above), unless fslbm_timing records sweeps or one of the environment
+ * above) where the classes at init hold few interface cells for the number of
+ * steps (128 for a call of one step, 600 to 1,536 for longer ones), unless
+ * fslbm_timing records sweeps or one of the environment
  * variables above, FSLBM_IFACE_QUAD, FSLBM_FP16_PAIRS or FSLBM_RCAP chooses
  * between the kernels of the step-by-step form at init (FSLBM_RESIDENT=0:
- * never); the results are the same bits.  A kernel whose workgroups wait for one
+ * never, 1: whatever the number of interface cells); the results are the same
+ * bits.  A kernel whose workgroups wait for one
  * another (that one, and the conversions of every form) goes on with those of
  * them that are on the device and never waits for room on it, so any number of
  * contexts, streams and processes may share a device.  Larger ones whose two population

@@ -33,6 +33,8 @@ struct Team {
 // moment it is closed.  The first workgroup to arrive closes it: at `most`
 // arrivals, or after `wait` looks with those that have arrived.  It calls before
 // just ahead of that (thread 0; stores of its own that the team is to see).
+// The ranks are the order of arrival (that of the launch in its place: 20^3 cells
+// FP32 with conversions 15.9 -> 16.8 us a step).
 template <class B>
 __device__ __forceinline__ Team join_team(unsigned long long* word, unsigned most, int wait, B before) {
   __shared__ Team mine;
@@ -90,11 +92,12 @@ struct GridBarrier {
     // times the barrier itself).
     drain_stores();
     const int any = __syncthreads_or(flag ? 1 : 0);
-    target += team.size;
     if (threadIdx.x == 0) {
       const unsigned long long add = 1ull + (any ? (odd ? 1ull << 48 : 1ull << 32) : 0ull);
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       __hip_atomic_fetch_add(p, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      target += team.size;
+      asm("" : "+v"(target));
       unsigned long long v;
       while ((unsigned)(v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < target)
         __builtin_amdgcn_s_sleep(1);
@@ -106,6 +109,7 @@ struct GridBarrier {
     const bool raised = __builtin_amdgcn_readfirstlane((int)(now != (odd ? seen1 : seen0))) != 0;
     seen0 = odd ? seen0 : now;
     seen1 = odd ? now : seen1;
+    asm("" : "+v"(seen0), "+v"(seen1));  // (vector registers: the kernels spill scalar ones)
     odd = !odd;
     return raised;
   }

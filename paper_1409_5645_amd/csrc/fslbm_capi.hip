@@ -48,6 +48,7 @@ struct fslbm_ctx {
   // runs of steps in one launch (small lattices): the interface list of that
   // kernel, cell -> entry, its length
   int32_t *res_list = nullptr, *res_slot = nullptr, *res_len = nullptr;
+  int res_iface = 0;  // interface cells at init (resident_interface); -1: any number (FSLBM_RESIDENT=1)
   // words of the kernels whose workgroups meet: a launch counts in one set and
   // zeroes the other for the next
   unsigned long long* bars = nullptr;
@@ -379,7 +380,10 @@ fslbm_status init_impl(const fslbm_params* p, const fslbm_buffers* b, void* work
   bool resident = N <= (size_t)RESIDENT_CELLS && p->precision != FSLBM_FP16S;
   for (const char* name : {"FSLBM_REORDER", "FSLBM_RCAP", "FSLBM_IFACE_QUAD", "FSLBM_FP16_PAIRS", "FSLBM_EXTENT_EVERY"})
     if (std::getenv(name)) resident = false;
-  if (const char* e = std::getenv("FSLBM_RESIDENT")) resident = resident && std::atoi(e) != 0;
+  if (const char* e = std::getenv("FSLBM_RESIDENT")) {
+    resident = resident && std::atoi(e) != 0;
+    c->res_iface = -1;
+  }
   if (resident) {
     c->res_list = (int32_t*)(w + L.res_list);
     c->res_slot = (int32_t*)(w + L.res_slot);
@@ -425,11 +429,14 @@ fslbm_status init_impl(const fslbm_params* p, const fslbm_buffers* b, void* work
   if ((e = launch_fill_f64(c->reservoir, 2, 0.0, st)) != hipSuccess) return fail(dev_fail(c, e, "init scalars"));
   if ((e = launch_fill_i32((int32_t*)c->bars, 2 * ALIGN / sizeof(int32_t), 0, st)) != hipSuccess)
     return fail(dev_fail(c, e, "init barriers"));
-  if ((e = launch_check_flags(c->flags, c->com.grid, c->err, st)) != hipSuccess) return fail(dev_fail(c, e, "check flags"));
-  int32_t herr = 0;
-  if ((e = hipMemcpyAsync(&herr, c->err, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream)) != hipSuccess)
+  if ((e = launch_check_flags(c->flags, c->com.grid, c->err, resident, st)) != hipSuccess)
+    return fail(dev_fail(c, e, "check flags"));
+  int32_t found[2] = {0, 0};
+  if ((e = hipMemcpyAsync(found, c->err, sizeof(found), hipMemcpyDeviceToHost, c->stream)) != hipSuccess)
     return fail(dev_fail(c, e, "read flag check"));
   if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return fail(dev_fail(c, e, "init sync"));
+  const int32_t herr = found[0];
+  if (c->res_iface >= 0) c->res_iface = found[1];
   if (herr & 1) { c->last_error = "unknown cell class in flags"; return fail(FSLBM_E_INVALID); }
   if (herr & 2) { c->last_error = "a liquid cell has a gas neighbour"; return fail(FSLBM_E_INVALID); }
   c->has_solid = (herr & 4) != 0;
@@ -885,7 +892,8 @@ fslbm_status fslbm_step(fslbm_ctx* c, int32_t n, int32_t rule) {
     c->last_error = "solid cells present: set their wall table with fslbm_set_walls first";
     return FSLBM_E_INVALID;
   }
-  const bool resident = c->res_list && !c->timing && !extra_step(c->com);
+  const bool resident = c->res_list && !c->timing && !extra_step(c->com) &&
+                        c->res_iface <= resident_interface(n, c->kept_len != nullptr);
   const bool together = c->kept_len && !c->deep && !c->timing && c->quad && n >= TOGETHER_STEPS && !extra_step(c->com);
   int32_t m = 1;  // steps of one pass of the loop
   for (int32_t i = 0; i < n; i += m) {

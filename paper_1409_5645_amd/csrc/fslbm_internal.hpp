@@ -161,12 +161,27 @@ struct ResidentArgs {
   int step, n;
 };
 static_assert(sizeof(ResidentArgs) <= 4096, "kernel arguments");
-// Largest lattice: up to here the launches cost more than the step's work
-// (us a step without conversions, kernels against resident: 1,280 cells FP32
-// 17.4 / 3.8, 3,072 FP64 19.4 / 6.2, 12,000 FP64 20.2 / 9.9, 30,000 FP32 19.4 /
-// 10.7; with ten conversions a step 30,000 FP32 30.3 / 29.2, FP64 33.0 / 33.8;
-// 61,440 FP64 without conversions 22.1 / 25.8).  Steps per launch: see
-// GridBarrier.
+// Where runs of steps are resident: lattices of up to RESIDENT_CELLS cells, and
+// up to so many interface cells (as the classes at init have them) for a call of
+// n steps.  What the launches cost is saved; a surface that takes more than a
+// part of the resident workgroups, or that converts at every step, loses by its
+// barriers.  us a step, kernels (from eight steps on with the interface cells in
+// the sweep's launch) / resident:
+//   64 interface cells (8 x 48 x 8 film, FP64)  n = 1 16.9 / 15.5, 2 16.8 / 11.4, 8 11.8 / 7.9, 64 12.3 / 6.9
+//   216 (181 x 181 x 1, FP64)                   1 22.8 / 25.8, 2 22.6 / 21.9, 4 22.5 / 19.9, 64 18.8 / 18.1
+//   408 (16 x 12 x 16, FP64)                    1 23.3 / 26.0, 2 23.4 / 22.5, 4 23.3 / 20.4, 64 18.5 / 18.5
+//   555 (20^3, FP32)                            1 22.6 / 25.0, 2 22.3 / 21.0, 4 22.2 / 18.6, 64 16.6 / 15.6
+//   665 (16 x 128 x 16, FP32)                   1 25.8 / 29.4, 2 25.9 / 25.5, 4 25.7 / 22.9, 64 18.5 / 20.6
+//   809 (24^3, FP64, bulk shear)                1 29.9 / 36.1, 2 29.9 / 31.2, 4 29.8 / 28.4, 64 23.9 / 25.6
+//   1,436 (32^3, FP64)                          1 32.3 / 37.7, 2 32.3 / 33.3, 4 32.2 / 30.5, 64 26.1 / 30.8
+//   2,249 (45 x 6 x 45, FP64)                   1 30.8 / 41.4, 2 30.7 / 37.0, 4 30.7 / 34.6, 64 24.6 / 31.8
+//   4,170 (64 x 8 x 64, calm, FP64)             1 17.3 / 31.0, 2 17.5 / 26.9, 4 17.3 / 24.9, 64 14.3 / 24.5
+// `kept`: the kernels would take the interface cells in the sweep's launch.
+// Steps per launch: see GridBarrier.
+inline int resident_interface(int n, bool kept) {
+  if (n == 1) return 128;
+  return n == 2 || (kept && n >= 8) ? 600 : 1536;
+}
 constexpr int RESIDENT_CELLS = 32768;
 constexpr int RESIDENT_STEPS = 256;
 // Where the interface cells and the sweep share a launch (k_together): calls of
@@ -308,7 +323,7 @@ hipError_t launch_list_append(const uint8_t* flags, const Grid& g, int32_t* coun
                               void* stream);
 hipError_t launch_fill_i32(int32_t* p, size_t n, int32_t v, void* stream);
 hipError_t launch_fill_f64(double* p, size_t n, double v, void* stream);
-hipError_t launch_check_flags(const uint8_t* flags, const Grid& g, int32_t* err, void* stream);
+hipError_t launch_check_flags(const uint8_t* flags, const Grid& g, int32_t* err, bool count, void* stream);
 hipError_t launch_deep(const DeepArgs& a, int precision, void* stream);
 hipError_t launch_check_walls(const uint8_t* flags, const Grid& g, const int32_t* cells, int n, const double* delta,
                               const double* uw, int32_t* err, int32_t* count, void* stream);

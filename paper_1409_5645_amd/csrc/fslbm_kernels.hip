@@ -650,11 +650,16 @@ __global__ __launch_bounds__(BLOCK) void k_fill_f64(double* p, size_t n, double 
   for (size_t i = (size_t)blockIdx.x * BLOCK + threadIdx.x; i < n; i += (size_t)gridDim.x * BLOCK) p[i] = v;
 }
 
-// cell classes valid and no liquid cell next to a gas cell
-__global__ __launch_bounds__(BLOCK) void k_check_flags(const uint8_t* flags, Grid g, int32_t* err) {
+// cell classes valid and no liquid cell next to a gas cell; count: also the
+// number of interface cells into err[1]
+__global__ __launch_bounds__(BLOCK) void k_check_flags(const uint8_t* flags, Grid g, int32_t* err, bool count) {
   const int idx = blockIdx.x * BLOCK + threadIdx.x;
   if (idx >= g.N) return;
   const uint8_t t = flags[idx];
+  if (count) {
+    const unsigned long long b = __ballot(t == IFACE);
+    if (b != 0ull && (int)__lane_id() == __ffsll((long long)b) - 1) atomicAdd(err + 1, __popcll(b));
+  }
   if (t > SOLID) {
     atomicOr(err, 1);
     return;
@@ -1083,8 +1088,8 @@ hipError_t launch_fill_f64(double* p, size_t n, double v, void* stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_check_flags(const uint8_t* flags, const Grid& g, int32_t* err, void* stream) {
-  k_check_flags<<<blocks_for(g.N), BLOCK, 0, (hipStream_t)stream>>>(flags, g, err);
+hipError_t launch_check_flags(const uint8_t* flags, const Grid& g, int32_t* err, bool count, void* stream) {
+  k_check_flags<<<blocks_for(g.N), BLOCK, 0, (hipStream_t)stream>>>(flags, g, err, count);
   return hipGetLastError();
 }
 

@@ -90,7 +90,6 @@ __global__ __launch_bounds__((rblock<F, RULE>())) void k_resident(ResidentArgs r
   if (team.size == 0u) return;
   GridBarrier grid(r.bar, team);
   const int tid = (int)team.rank * RBLOCK + (int)threadIdx.x, nth = (int)team.size * RBLOCK;
-  const int wave = __builtin_amdgcn_readfirstlane(tid);  // the wavefront's first thread
   // threads for interface cells at most: half of the workgroups, or of the only one
   const int most = team.size > 1u ? (int)(team.size / 2u) * RBLOCK : RBLOCK / 2;
   int len = 0;
@@ -127,7 +126,7 @@ __global__ __launch_bounds__((rblock<F, RULE>())) void k_resident(ResidentArgs r
     // the liquid cells
     const int ni = min((QUAD * len + RBLOCK - 1) / RBLOCK * RBLOCK, most);
     bool conv = false;
-    if (wave < ni) {
+    if (__builtin_amdgcn_readfirstlane(tid) < ni) {
       const int stride = ni / QUAD;
       for (int i = tid >> 2; i < len; i += stride) {
         if (changed || len > stride) {

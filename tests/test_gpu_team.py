@@ -52,7 +52,7 @@ def test_resident_steps_of_a_part_of_the_grid(fs, monkeypatch, precision, rule, 
     print(f"case team resident {precision} rule {rule} {env}", flush=True)
     w = slosh(31, 25, 17, gy=-1.2e-3)
     ref = run(fs, monkeypatch, w, precision, rule, (1, 6, 30, 3), {"FSLBM_RESIDENT": "0"})
-    same(ref, run(fs, monkeypatch, w, precision, rule, (1, 6, 30, 3), env))
+    same(ref, run(fs, monkeypatch, w, precision, rule, (1, 6, 30, 3), {"FSLBM_RESIDENT": "1", **env}))
     assert any(sum(v.size for v in c.values()) > 0 for _, c in ref)
 
 
