@@ -98,9 +98,10 @@ __global__ __launch_bounds__(DeepTile<F>::THREADS) void k_deep(DeepArgs a) {
   auto load = [&](int z) __attribute__((always_inline)) {  // pulls of plane z
     const int zm = step_axis(z, -1, g.nz, g.pz), zp = step_axis(z, 1, g.nz, g.pz);
     if (inner && (zm | zp) >= 0) {
+      const unsigned om = (unsigned)zm * nxy, o0 = (unsigned)z * nxy, op = (unsigned)zp * nxy;
 #define FSLBM_DPULL(q)                                                                                      \
   {                                                                                                         \
-    const long long b = deep_base(q, CX[q], CY[q], CZ[q] == 1 ? zm : (CZ[q] == -1 ? zp : z), g.nx, nxy, N);  \
+    const long long b = deep_base(q, CX[q], CY[q], CZ[q] == 1 ? om : (CZ[q] == -1 ? op : o0), g.nx, N);      \
     r[q] = F::load_raw(reinterpret_cast<const S*>(reinterpret_cast<const char*>(fin + b) + sb));            \
   }
       FSLBM_DPULL(0)
@@ -112,7 +113,7 @@ __global__ __launch_bounds__(DeepTile<F>::THREADS) void k_deep(DeepArgs a) {
     const int sx = CX[q] == 1 ? xm : (CX[q] == -1 ? xp : x);                                        \
     const int sy = CY[q] == 1 ? ym : (CY[q] == -1 ? yp : y);                                        \
     const int sz = CZ[q] == 1 ? zm : (CZ[q] == -1 ? zp : z);                                        \
-    r[q] = F::load_raw(fin + deep_source(q, OPP[q], sx, sy, sz, x, y, z, (unsigned)g.nx, nxy, N));   \
+    r[q] = F::load_raw(fin + deep_source(q, OPP[q], sx, sy, sz, self, z, g.nx, nxy, N));             \
   }
       FSLBM_DPULL(0)
       FSLBM_LINKS(FSLBM_DPULL)

@@ -66,17 +66,18 @@ constexpr int deep_wrap(int v, int n, bool periodic) {
 constexpr int deep_row(int y, int yd) { return y < 0 ? 0 : (y < yd ? y : yd); }
 
 // Element that the pull of a link reads: from the cell x - c, or (a coordinate
-// of it is -1: beyond a wall) the cell's own population opp.
-constexpr unsigned deep_source(int q, int opp, int sx, int sy, int sz, int x, int y, int z, unsigned nx, unsigned nxy,
+// of it is -1: beyond a wall) the cell's own population opp.  self = x + nx y.
+constexpr unsigned deep_source(int q, int opp, int sx, int sy, int sz, unsigned self, int z, int nx, unsigned nxy,
                                unsigned N) {
-  return (sx | sy | sz) < 0 ? (unsigned)opp * N + (unsigned)z * nxy + ((unsigned)x + nx * (unsigned)y)
-                            : (unsigned)q * N + (unsigned)sz * nxy + ((unsigned)sx + nx * (unsigned)sy);
+  return (sx | sy | sz) < 0 ? (unsigned)opp * N + (unsigned)z * nxy + self
+                            : (unsigned)q * N + (unsigned)sz * nxy + (unsigned)(sx + nx * sy);
 }
 
 // The same where no link of the wavefront wraps or leaves the lattice within
-// its plane: the element is this base (uniform) plus x + nx y.
-constexpr long long deep_base(int q, int cx, int cy, int sz, int nx, unsigned nxy, unsigned N) {
-  return (long long)((unsigned)q * N + (unsigned)sz * nxy) - (cx + (long long)nx * cy);
+// its plane, which begins at element `plane` of a population: the element is this
+// base (uniform) plus self.
+constexpr long long deep_base(int q, int cx, int cy, unsigned plane, int nx, unsigned N) {
+  return (long long)((unsigned)q * N + plane) - (cx + nx * cy);
 }
 
 }  // namespace fslbm

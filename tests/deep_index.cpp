@@ -55,9 +55,9 @@ int main(int, char** a) {
             const int sx = step(x, -c[0], nx, px), sy = y - c[1] < 0 ? -1 : y - c[1], sz = c[2] == 1 ? zm : (c[2] == -1 ? zp : z);
             long long e;
             if (inner && (zm | zp) >= 0)
-              e = deep_base(q, c[0], c[1], sz, nx, (unsigned)nxy, (unsigned)N) + x + (long long)nx * y;
+              e = deep_base(q, c[0], c[1], (unsigned)(sz * nxy), nx, (unsigned)N) + x + (long long)nx * y;
             else
-              e = deep_source(q, opp, sx, sy, sz, x, y, z, (unsigned)nx, (unsigned)nxy, (unsigned)N);
+              e = deep_source(q, opp, sx, sy, sz, (unsigned)(x + nx * y), z, nx, (unsigned)nxy, (unsigned)N);
             if (e < 0 || e >= 19 * N) ++out;
             // the pull, from the unwrapped cell
             if (used && Z <= z1 && (Z >= 0 || pz) && (Z < nz || pz)) {
