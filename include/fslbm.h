@@ -160,7 +160,12 @@ typedef struct {
  * interface-first step of fslbm_step; up to 32,768 cells also the interface list
  * of the one-launch form; where population buffers are 300 MB to 17 GB each and
  * y is not periodic, no wall moves and the equilibrium is the incompressible one
- * with its quadratic term, a third population buffer for the two-step kernel). */
+ * with its quadratic term, a third population buffer for the two-step kernel).
+ * fslbm_init also takes a workspace without that third buffer (19 N elements of
+ * the storage type less), or without the lists of the one-launch form and of the
+ * step with the interface cells in the sweep's launch (in the FP16 form 4 N bytes
+ * and up to 32,768 cells in the other forms 12 N bytes less, each rounded up to
+ * 256); its context then steps without those kernels, with the same results. */
 fslbm_status fslbm_workspace_size(const fslbm_params* p, size_t* bytes);
 
 /* Validate parameters and buffers, check the cell classes on the device (every
@@ -173,8 +178,8 @@ fslbm_status fslbm_init(const fslbm_params* p, const fslbm_buffers* b, fslbm_ctx
 
 /* Size of the library's static workspace of fslbm_init_static (64 MiB per
  * device: about 880,000 cells without surface tension; a static context needs
- * less than fslbm_workspace_size, as it always runs the interface kernel after
- * the sweep). */
+ * less than fslbm_workspace_size: beyond the one-launch form of lattices of up to
+ * 32,768 cells it runs the interface kernel after the sweep). */
 #define FSLBM_STATIC_WORKSPACE_BYTES (64u << 20)
 
 /* For callers that cannot allocate device memory (tight serving loops,

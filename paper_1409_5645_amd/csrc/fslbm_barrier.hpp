@@ -16,9 +16,9 @@ namespace fslbm {
 // before it in the program comes before it).
 __device__ __forceinline__ void drain_stores() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
 
-// A launch has two words, zero at its start: the barrier's (GridBarrier) and,
-// TEAM_WORD further (another line), the team's.
-constexpr int TEAM_WORD = 16;
+// A launch has BAR_WORDS words, zero at its start: the barrier's (GridBarrier)
+// and, TEAM_WORD further, the team's.
+constexpr int BAR_WORDS = 2, TEAM_WORD = 1;
 // Looks of a team's first workgroup at the number of arrivals before it closes
 // the team, each some tenths of a microsecond after the last: a grid that finds
 // room starts well within one look.

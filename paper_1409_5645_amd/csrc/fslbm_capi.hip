@@ -135,11 +135,12 @@ void wall_table(const fslbm_params& p, double out[6 * Q]) {
 // kappa: with surface tension, one Laplace-pressure correction per listed cell;
 // hf: with surface tension and plic = 2, the height-function kappa per cell;
 // reorder: room for the interface-first step (cell -> list entry, 19
-// populations of s bytes per list entry); lattices of up to RESIDENT_CELLS
-// also (not in the FP16 form) have the list of the resident step; third: a
-// third population buffer, for the two-step kernel; kept: room for the list
-// that k_together's steps keep (its map is islot's where there is one)
-Layout layout(size_t N, bool kappa, bool hf, size_t s, bool reorder, bool third, bool kept) {
+// populations of s bytes per list entry).  What a context can do without (the
+// faster routes of some lattices) comes last: resident, the list of the resident
+// step (lattices of up to RESIDENT_CELLS, not in the FP16 form); kept, room for
+// the list that k_together's steps keep (its map is islot's where there is one);
+// third, a third population buffer for the two-step kernel.
+Layout layout(size_t N, bool kappa, bool hf, size_t s, bool reorder, bool resident, bool kept, bool third) {
   Layout L{};
   size_t o = 0;
   L.aux = o;
@@ -154,6 +155,10 @@ Layout layout(size_t N, bool kappa, bool hf, size_t s, bool reorder, bool third,
   }
   L.counters = o;
   o = align_up(o + 2 * NCOUNT * sizeof(int32_t));
+  // the words of the kernels whose workgroups meet: in a line of their own of
+  // the counters' 256 bytes
+  static_assert(2 * NCOUNT * sizeof(int32_t) <= 128 && 2 * BAR_WORDS * sizeof(unsigned long long) <= 128, "lines");
+  L.bars = L.counters + 128;
   L.scalars = o;  // reservoir, acc, err(int), cnt[8] (int)
   o = align_up(o + 2 * sizeof(double) + 16 * sizeof(int32_t));
   L.extent = o;
@@ -169,7 +174,7 @@ Layout layout(size_t N, bool kappa, bool hf, size_t s, bool reorder, bool third,
   if (reorder) o = align_up(o + 4 * N);
   L.rbuf = o;
   if (reorder) o = align_up(o + (size_t)Q * s * L.rcap);
-  const bool small = N <= (size_t)RESIDENT_CELLS && s != storage_bytes(FSLBM_FP16S);
+  const bool small = resident && N <= (size_t)RESIDENT_CELLS && s != storage_bytes(FSLBM_FP16S);
   L.res_list = o;
   if (small) o = align_up(o + 8 * N);
   L.res_slot = o;
@@ -180,8 +185,6 @@ Layout layout(size_t N, bool kappa, bool hf, size_t s, bool reorder, bool third,
   if (kept) o = align_up(o + NCOUNT * sizeof(int32_t));
   L.kept_slot = reorder ? L.islot : o;
   if (kept && !reorder) o = align_up(o + 4 * N);
-  L.bars = o;
-  o = align_up(o + 2 * ALIGN);
   L.third = o;
   if (third) o = align_up(o + (size_t)Q * s * N);
   L.total = o;
@@ -306,7 +309,7 @@ fslbm_status fslbm_workspace_size(const fslbm_params* p, size_t* bytes) {
   if (s != FSLBM_OK) { g_init_error = why; return s; }
   if (!bytes) { g_init_error = "bytes is NULL"; return FSLBM_E_INVALID; }
   *bytes = layout((size_t)p->nx * p->ny * p->nz, p->sigma != 0.0, p->plic == 2, storage_bytes(p->precision),
-                  p->precision != FSLBM_FP16S, deep_lattice(*p), true).total;
+                  p->precision != FSLBM_FP16S, true, true, deep_lattice(*p)).total;
   return FSLBM_OK;
 }
 
@@ -317,13 +320,13 @@ namespace {
 // fslbm_init with the workspace given separately (the caller's buffer, or the
 // library's static array for fslbm_init_static); parameters already checked.
 fslbm_status init_impl(const fslbm_params* p, const fslbm_buffers* b, void* workspace, size_t workspace_bytes,
-                       bool reorder, bool third, bool kept, fslbm_ctx** out) {
+                       bool reorder, bool lists, bool kept, bool third, fslbm_ctx** out) {
   if (!b->f[0] || !b->f[1] || !b->flags || !b->mass || !b->phi[0] || !b->phi[1] || !workspace) {
     g_init_error = "a device buffer is NULL";
     return FSLBM_E_INVALID;
   }
   const size_t N = (size_t)p->nx * p->ny * p->nz;
-  const Layout L = layout(N, p->sigma != 0.0, p->plic == 2, storage_bytes(p->precision), reorder, third, kept);
+  const Layout L = layout(N, p->sigma != 0.0, p->plic == 2, storage_bytes(p->precision), reorder, lists, kept, third);
   if (workspace_bytes < L.total) { g_init_error = "workspace too small"; return FSLBM_E_INVALID; }
   if (((uintptr_t)workspace) % ALIGN) { g_init_error = "workspace not 256-byte aligned"; return FSLBM_E_INVALID; }
 
@@ -377,7 +380,7 @@ fslbm_status init_impl(const fslbm_params* p, const fslbm_buffers* b, void* work
   }
   // The resident step, unless the environment chooses the layout or order of
   // the kernels of the step-by-step form (FSLBM_RESIDENT=0: never)
-  bool resident = N <= (size_t)RESIDENT_CELLS && p->precision != FSLBM_FP16S;
+  bool resident = lists && N <= (size_t)RESIDENT_CELLS && p->precision != FSLBM_FP16S;
   for (const char* name : {"FSLBM_REORDER", "FSLBM_RCAP", "FSLBM_IFACE_QUAD", "FSLBM_FP16_PAIRS", "FSLBM_EXTENT_EVERY"})
     if (std::getenv(name)) resident = false;
   if (const char* e = std::getenv("FSLBM_RESIDENT")) {
@@ -427,7 +430,7 @@ fslbm_status init_impl(const fslbm_params* p, const fslbm_buffers* b, void* work
   if ((e = launch_fill_i32(c->err, 16, 0, st)) != hipSuccess) return fail(dev_fail(c, e, "init scalars"));
   if ((e = launch_extent_init(c->ext_dev, st)) != hipSuccess) return fail(dev_fail(c, e, "init extent"));
   if ((e = launch_fill_f64(c->reservoir, 2, 0.0, st)) != hipSuccess) return fail(dev_fail(c, e, "init scalars"));
-  if ((e = launch_fill_i32((int32_t*)c->bars, 2 * ALIGN / sizeof(int32_t), 0, st)) != hipSuccess)
+  if ((e = launch_fill_i32((int32_t*)c->bars, 2 * BAR_WORDS * sizeof(unsigned long long) / sizeof(int32_t), 0, st)) != hipSuccess)
     return fail(dev_fail(c, e, "init barriers"));
   if ((e = launch_check_flags(c->flags, c->com.grid, c->err, resident, st)) != hipSuccess)
     return fail(dev_fail(c, e, "check flags"));
@@ -464,8 +467,16 @@ fslbm_status fslbm_init(const fslbm_params* p, const fslbm_buffers* b, fslbm_ctx
   fslbm_status s = check_params(p, why);
   if (s != FSLBM_OK) { g_init_error = why; return s; }
   if (!b || !out) { g_init_error = "buffers or out is NULL"; return FSLBM_E_INVALID; }
-  // the interface-first buffers: FP32 and FP64 forms (FP16 keeps the other order)
-  s = init_impl(p, b, b->workspace, b->workspace_bytes, p->precision != FSLBM_FP16S, deep_lattice(*p), true, out);
+  // the interface-first buffers: FP32 and FP64 forms (FP16 keeps the other order);
+  // a workspace too small for the two-step kernel's buffer, or for the lists of
+  // the resident and the joint step, does without
+  const bool first = p->precision != FSLBM_FP16S;
+  auto fits = [&](bool lists, bool third) {
+    return b->workspace_bytes >= layout((size_t)p->nx * p->ny * p->nz, p->sigma != 0.0, p->plic == 2,
+                                        storage_bytes(p->precision), first, lists, lists, third).total;
+  };
+  const bool lists = fits(true, false), third = deep_lattice(*p) && fits(true, true);
+  s = init_impl(p, b, b->workspace, b->workspace_bytes, first, lists, lists, third, out);
   if (s != FSLBM_OK) return s;
   fslbm_ctx* c = *out;
   // the two-step kernel's rows shrink by a row for every step since the
@@ -493,7 +504,7 @@ fslbm_status fslbm_init_static(const fslbm_params* p, const fslbm_buffers* b, fs
   if (s != FSLBM_OK) { g_init_error = why; return s; }
   if (!b || !out) { g_init_error = "buffers or out is NULL"; return FSLBM_E_INVALID; }
   const size_t need =
-      layout((size_t)p->nx * p->ny * p->nz, p->sigma != 0.0, p->plic == 2, storage_bytes(p->precision), false, false, false).total;
+      layout((size_t)p->nx * p->ny * p->nz, p->sigma != 0.0, p->plic == 2, storage_bytes(p->precision), false, true, false, false).total;
   if (need > (size_t)FSLBM_STATIC_WORKSPACE_BYTES) {
     g_init_error = "the lattice needs " + std::to_string(need) + " bytes of workspace, more than the " +
                    std::to_string((size_t)FSLBM_STATIC_WORKSPACE_BYTES) + " of the static workspace";
@@ -519,7 +530,7 @@ fslbm_status fslbm_init_static(const fslbm_params* p, const fslbm_buffers* b, fs
     ws = g_scratch_ptr[dev];
     g_scratch_busy[dev] = true;
   }
-  s = init_impl(p, b, ws, (size_t)FSLBM_STATIC_WORKSPACE_BYTES, false, false, false, out);
+  s = init_impl(p, b, ws, (size_t)FSLBM_STATIC_WORKSPACE_BYTES, false, true, false, false, out);
   std::lock_guard<std::mutex> lock(g_scratch_mu);
   if (s != FSLBM_OK) g_scratch_busy[dev] = false;
   else (*out)->static_device = dev;
@@ -738,8 +749,8 @@ void step_args(const fslbm_ctx* c, StepLaunch& L) {
   v.listI = c->listI;
   v.islot = c->islot;
   v.counters_next = s.counters_next;
-  v.bar = c->bars + c->bar_flip * (ALIGN / sizeof(unsigned long long));
-  v.bar_next = c->bars + (1 - c->bar_flip) * (ALIGN / sizeof(unsigned long long));
+  v.bar = c->bars + c->bar_flip * BAR_WORDS;
+  v.bar_next = c->bars + (1 - c->bar_flip) * BAR_WORDS;
   v.team = c->team;
   v.team_wait = c->team_wait;
   s.islot = c->islot;
