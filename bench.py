@@ -82,7 +82,11 @@ def run_form(w, form, steps, warmup, rule, log, roof_steps=500):
     with nothing but the step kernels in the queue (the whole-step rate), and
     min(steps, roof_steps) more with HIP events around every sweep launch (its
     average duration for the roofline).  The events of the second region cost
-    a few microseconds per step, so they stay out of the first."""
+    a few microseconds per step, so they stay out of the first; and its steps
+    are taken one at a time, while FP64 and FP32 steps of the first take two at
+    once below the surface.  So the sweep's figures (sweep_ms, sweep_share,
+    sweep_gbs) are those of the second region, and step_gbs of these two forms
+    credits 38 values a step to a route that moves about half of them."""
     import torch
     from paper_1409_5645_amd import fslbm
     t0 = time.time()
@@ -119,7 +123,7 @@ def run_form(w, form, steps, warmup, rule, log, roof_steps=500):
         "mlups_all_cells": w.params.n_cells / (ms * 1e-3) / 1e6,
         "ms_per_step": ms,
         "sweep_ms": sweep_avg,
-        "sweep_share": sweep_avg / ms,
+        "sweep_share": sweep_avg / (ms_roof / n_roof),  # of a step of its own region
         "sweep_timed_steps": n_roof,
         "ms_per_step_with_sweep_events": ms_roof / n_roof,
         "active_cells": n_act,
@@ -362,7 +366,8 @@ def main():
             "bytes_per_launch": r["alg_bytes_per_sweep"], "avg_launch_ms": r["sweep_ms"],
             "timed_launches": r["sweep_timed_steps"],
             # the sweep's algorithmic bytes over the whole step (interface and
-            # conversion kernels included)
+            # conversion kernels included); where two steps are taken at once
+            # (FP64, FP32) they are more than the step moves
             "step_frac": r["step_gbs"] / HBM_PEAK_GBS}
     for form in forms:
         results[form]["roofline_frac"] = results[form]["sweep_gbs"] / HBM_PEAK_GBS

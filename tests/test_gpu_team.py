@@ -81,3 +81,29 @@ def test_conversions_of_a_part_of_the_grid(fs, oracle_mod, monkeypatch, precisio
         act = g["flags"] != W.GAS
         assert np.array_equal(g["flags"], o.flags())
         assert np.array_equal(g["f"][:, act], o.populations()[:, act])
+
+
+def test_eight_contexts_share_the_device(fs, monkeypatch):
+    """Resident steps whose workgroups take a compute unit each (FP64, boundary shear from the bulk) and
+    conversions of larger lattices, on eight streams at once: each as alone."""
+    import torch
+    for k in ("FSLBM_TEAM", "FSLBM_TEAM_WAIT"):
+        monkeypatch.delenv(k, raising=False)
+    monkeypatch.setenv("FSLBM_RESIDENT", "1")
+    loads = [(slosh(31, 25, 17, gy=-1.2e-3), 3), (slosh(48, 40, 44, gy=-6e-4), 1)]
+    refs = []
+    for w, rule in loads:
+        s = fs.Sim.from_workload(w)
+        s.step(60, rule)
+        refs.append(s.fields(("f", "flags")))
+        s.close()
+    sims = [(i % 2, fs.Sim.from_workload(loads[i % 2][0], stream=torch.cuda.Stream())) for i in range(8)]
+    for _ in range(6):
+        for k, s in sims:
+            s.step(10, loads[k][1])
+    for k, s in sims:
+        g = s.fields(("f", "flags"))
+        act = refs[k]["flags"] != W.GAS
+        assert np.array_equal(g["flags"], refs[k]["flags"])
+        assert np.array_equal(g["f"][:, act], refs[k]["f"][:, act])
+        s.close()
